@@ -4,12 +4,19 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libdg.so")
-SOURCES = ["dg_api.hip", "dg_host.cpp", "dg_mfma_host.cpp"]
+# translation units: source and its own flags; dg_stage.hip holds the kernels
+# of one order (in parts: BF16x3, FP32, FP64, adjoint), so that they compile
+# in parallel, the slowest first
+SOURCES = [("dg_stage.hip", [f"-DDG_ORDER={n}", f"-DDG_PART={p}"])
+           for n in (4, 3, 2, 7, 6, 5, 1) for p in ((3, 2, 1, 0) if n <= 4 else (2, 1, 0))] + [
+    ("dg_api.hip", []), ("dg_host.cpp", []), ("dg_mfma_host.cpp", [])]
 
 HIPCC_FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "-shared", "--offload-arch=gfx950",
@@ -30,15 +37,27 @@ def hipcc():
 
 
 def build(verbose: bool = False) -> str:
-    srcs = [os.path.join(CSRC, s) for s in SOURCES]
+    common = [hipcc()] + HIPCC_FLAGS + ["-I", os.path.join(ROOT, "include")]
+    jobs = int(os.environ.get("MAX_JOBS") or min(16, os.cpu_count() or 1))
     tmp = LIB + ".tmp"
-    cmd = [hipcc()] + HIPCC_FLAGS + ["-I", os.path.join(ROOT, "include"), "-o", tmp] + srcs
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    if r.returncode != 0:
-        sys.stderr.write(r.stdout + r.stderr)
-        raise RuntimeError("hipcc failed building libdg.so")
+    with tempfile.TemporaryDirectory() as objs:
+        def run(cmd):
+            if verbose:
+                print(" ".join(cmd), flush=True)
+            r = subprocess.run(cmd, capture_output=True, text=True)
+            if r.returncode != 0:
+                sys.stderr.write(r.stdout + r.stderr)
+                raise RuntimeError("hipcc failed building libdg.so")
+
+        def compile_one(item):
+            i, (src, flags) = item
+            obj = os.path.join(objs, f"{i}.o")
+            run([f for f in common if f != "-shared"] + flags +
+                ["-c", "-o", obj, os.path.join(CSRC, src)])
+            return obj
+        with ThreadPoolExecutor(max_workers=jobs) as pool:
+            done = list(pool.map(compile_one, enumerate(SOURCES)))
+        run(common + ["-o", tmp] + done)
     os.replace(tmp, LIB)
     return LIB
 

@@ -700,7 +700,7 @@ struct NodeArgs {
   int upwind;
 };
 
-__global__ __launch_bounds__(256) void adj_nodes(NodeArgs A) {
+static __global__ __launch_bounds__(256) void adj_nodes(NodeArgs A) {
   const int Np = A.Np, Nfp = A.Nfp, NF4 = 4 * Nfp;
   const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   const int64_t K = A.K, KNp = K * Np;

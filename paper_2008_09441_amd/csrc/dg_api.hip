@@ -22,6 +22,7 @@
 #include "dg_adj.hpp"
 #include "dg_adjt.hpp"
 #include "dg_batch.hpp"
+#include "dg_launch.hpp"
 #include "dg_peaks.hpp"
 #include "dg_mfma_host.hpp"
 
@@ -259,8 +260,7 @@ hipError_t launch_mfma_d(const dg_ctx* c, const double* q_in, double* q_out, dou
   A.upwind = c->opt.flux == DG_FLUX_UPWIND ? 1 : 0;
   const int64_t tiles = (c->mesh.K + dgb::kTile - 1) / dgb::kTile;
   if (tiles > 0x7fffffff) return hipErrorInvalidValue;
-  dgb::stage_bx_d<N><<<dim3(unsigned(tiles)), dim3(dgb::kThreads), 0, c->stream>>>(A);
-  return hipGetLastError();
+  return dgl::stage_bx_d<N>(A, unsigned(tiles), c->stream);
 }
 
 // FP64 stage on the matrix cores at orders 5-7: one element per workgroup
@@ -290,8 +290,7 @@ hipError_t launch_be_d(const dg_ctx* c, const double* q_in, double* q_out, doubl
   A.lsrk = lsrk;
   A.upwind = c->opt.flux == DG_FLUX_UPWIND ? 1 : 0;
   if (c->mesh.K > 0x7fffffff) return hipErrorInvalidValue;
-  dgb::stage_be_d<N><<<dim3(unsigned(c->mesh.K)), dim3(dgb::kThreads), 0, c->stream>>>(A);
-  return hipGetLastError();
+  return dgl::stage_be_d<N>(A, unsigned(c->mesh.K), c->stream);
 }
 
 // FP64 contexts: the matrix-core kernels in double precision (the tiled
@@ -351,10 +350,9 @@ hipError_t launch_mfma_n(dg_ctx* c, const float* q_in, float* q_out, float* res,
   A.r_out = r_out;
   A.j_out = j_out;
   if constexpr (RST)
-    dgb::stage_bx_r<N><<<dim3(unsigned(tiles)), dim3(dgb::kThreads), 0, c->stream>>>(A);
+    return dgl::stage_bx_r<N>(A, unsigned(tiles), c->stream);
   else
-    dgb::stage_bx<N, F32><<<dim3(unsigned(tiles)), dim3(dgb::kThreads), 0, c->stream>>>(A);
-  return hipGetLastError();
+    return dgl::stage_bx<N, F32>(A, unsigned(tiles), c->stream);
 }
 
 template <int N, bool F32>
@@ -383,8 +381,7 @@ hipError_t launch_mfma_e(dg_ctx* c, const float* q_in, float* q_out, float* res,
   A.upwind = c->opt.flux == DG_FLUX_UPWIND ? 1 : 0;
   // one workgroup per element
   if (c->mesh.K > 0x7fffffff) return hipErrorInvalidValue;
-  dgb::stage_be<N, F32><<<dim3(unsigned(c->mesh.K)), dim3(dgb::kThreads), 0, c->stream>>>(A);
-  return hipGetLastError();
+  return dgl::stage_be<N, F32>(A, unsigned(c->mesh.K), c->stream);
 }
 
 dg_status launch_mfma(dg_ctx* c, const void* q_in, void* q_out, void* res, void* rhs_out,
@@ -680,15 +677,6 @@ dg_status adj_tables(dg_ctx* c) {
   return upload_raw(c, c->adj_invf, invf.data(), invf.size());
 }
 
-// one reverse stage on the tiled adjoint kernels (FP32, orders 1-4): lres
-// = a lres + b ly, the gradient terms, then ly += dt R^T W^T lres and the
-// impedance gradient
-template <int N>
-void launch_adj_tile(dg_ctx* c, const dgt::TileArgs& A) {
-  const unsigned tiles = unsigned((A.K + 15) / 16);
-  hipLaunchKernelGGL((dgt::adj_tile<N, true>), dim3(tiles), dim3(dgt::kThreads), 0, c->stream, A);
-}
-
 // one FP32 stage of the replay (fused LSRK update) that also stores R q_in
 // and, if j_out is not null, the jumps at its face nodes
 dg_status stage_raw(dg_ctx* c, const void* q_in, void* q_out, void* res, void* r_out,
@@ -710,6 +698,9 @@ dg_status stage_raw(dg_ctx* c, const void* q_in, void* q_out, void* res, void* r
   return DG_OK;
 }
 
+// one reverse stage on the tiled adjoint kernels (FP32, orders 1-4): lres
+// = a lres + b ly, the gradient terms, then ly += dt R^T W^T lres and the
+// impedance gradient.
 // jin: the stage input's face-node jumps as the replay stored them, or null
 // (the tile kernel then computes them from y into adj_zb)
 dg_status adj_stage_tiled(dg_ctx* c, const float* y, const float* r, const float* jin,
@@ -747,14 +738,16 @@ dg_status adj_stage_tiled(dg_ctx* c, const float* y, const float* r, const float
   A.jumps = jin ? 0 : 1;
   if (!A.nbn || !A.mat || !A.frags || !A.fmask || !A.r)
     return fail(c, DG_ESTATE, "adjoint: tiled kernel tables missing");
+  const unsigned tiles = unsigned((K + 15) / 16);
+  hipError_t e = hipSuccess;
   switch (c->re.N) {
-    case 1: launch_adj_tile<1>(c, A); break;
-    case 2: launch_adj_tile<2>(c, A); break;
-    case 3: launch_adj_tile<3>(c, A); break;
-    case 4: launch_adj_tile<4>(c, A); break;
+    case 1: e = dgl::adj_tile<1>(A, tiles, c->stream); break;
+    case 2: e = dgl::adj_tile<2>(A, tiles, c->stream); break;
+    case 3: e = dgl::adj_tile<3>(A, tiles, c->stream); break;
+    case 4: e = dgl::adj_tile<4>(A, tiles, c->stream); break;
     default: return fail(c, DG_EINVAL, "adjoint: no tiled kernel at this order");
   }
-  DG_HIP(c, hipGetLastError());
+  DG_HIP(c, e);
   dgt::NodeArgs B{};
   B.nu = nu;
   B.gf = A.gf;
@@ -1042,25 +1035,13 @@ dg_status exception_status() {
 // arguments, then each step runs five stage launches, five source launches
 // and one receiver launch for the whole batch.
 
-template <int N, bool F32>
-hipError_t launch_batch_stage(const dgb::BatchSlot* table, int n, int64_t grid, hipStream_t st,
-                              int par, double a, double b) {
-  if constexpr (N <= 4)
-    dgb::stage_bx_batch<N, F32><<<dim3(unsigned(grid)), dim3(dgb::kThreads), 0, st>>>(
-        table, n, par, float(a), float(b));
-  else
-    dgb::stage_be_batch<N, F32><<<dim3(unsigned(grid)), dim3(dgb::kThreads), 0, st>>>(
-        table, n, par, float(a), float(b));
-  return hipGetLastError();
-}
-
 hipError_t batch_stage(int N, bool f32, const dgb::BatchSlot* table, int n, int64_t grid,
                        hipStream_t st, int par, double a, double b) {
   switch (N) {
 #define DG_BATCH_CASE(NN)                                                                  \
   case NN:                                                                                 \
-    return f32 ? launch_batch_stage<NN, true>(table, n, grid, st, par, a, b)              \
-               : launch_batch_stage<NN, false>(table, n, grid, st, par, a, b);
+    return f32 ? dgl::stage_batch<NN, true>(table, n, unsigned(grid), st, par, float(a), float(b)) \
+               : dgl::stage_batch<NN, false>(table, n, unsigned(grid), st, par, float(a), float(b));
     DG_BATCH_CASE(1)
     DG_BATCH_CASE(2)
     DG_BATCH_CASE(3)

@@ -95,7 +95,7 @@ __global__ __launch_bounds__(kThreads, 2) void stage_be_batch(const BatchSlot* s
 // t = clk[0] + frac dt, frac = i + c_s; one thread per (velocity component,
 // node), each looping over its slot's sources (the single-context kernel's
 // arithmetic, in the same order).
-__global__ void source_add_batch(const BatchSlot* slots, int par, double frac, double bcoef) {
+static __global__ void source_add_batch(const BatchSlot* slots, int par, double frac, double bcoef) {
   const BatchSlot& S = slots[blockIdx.y];
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (S.nsrc == 0 || i >= 3 * S.Np) return;
@@ -115,7 +115,7 @@ __global__ void source_add_batch(const BatchSlot* slots, int par, double frac, d
 
 // After step i, whose result is in q[par]: velocity at the receivers of slot
 // blockIdx.y into trace row clk[1] + i (rows past the capacity are skipped)
-__global__ void receiver_sample_batch(const BatchSlot* slots, int par, int64_t soff) {
+static __global__ void receiver_sample_batch(const BatchSlot* slots, int par, int64_t soff) {
   const BatchSlot& S = slots[blockIdx.y];
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (S.nrec == 0 || S.trace_cap == 0 || i >= 3 * S.nrec) return;
@@ -130,7 +130,7 @@ __global__ void receiver_sample_batch(const BatchSlot* slots, int par, int64_t s
 }
 
 // the device clocks of every slot advance by nsteps steps of their own dt
-__global__ void clock_advance_batch(const BatchSlot* slots, int nslots, int64_t nsteps) {
+static __global__ void clock_advance_batch(const BatchSlot* slots, int nslots, int64_t nsteps) {
   const int s = blockIdx.x * blockDim.x + threadIdx.x;
   if (s >= nslots) return;
   double* clk = slots[s].clk;
@@ -145,7 +145,7 @@ struct SlotChunk {
   uint32_t w[kSlotWords];
 };
 
-__global__ void slot_write(uint32_t* dst, SlotChunk chunk, int nwords) {
+static __global__ void slot_write(uint32_t* dst, SlotChunk chunk, int nwords) {
   for (int i = threadIdx.x; i < nwords; i += blockDim.x) dst[i] = chunk.w[i];
 }
 

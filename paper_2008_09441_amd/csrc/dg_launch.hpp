@@ -1,0 +1,34 @@
+// Launchers of the order-templated kernels.  Each order's kernels are
+// compiled in a translation unit of their own (dg_stage.hip with DG_ORDER
+// set), so that a build compiles the orders in parallel; callers see only
+// these declarations.
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include "dg_adjt.hpp"
+#include "dg_batch.hpp"
+#include "dg_be.hpp"
+#include "dg_bx.hpp"
+
+namespace dgl {
+
+// orders 1-4: `grid` element tiles
+template <int N, bool F32>
+hipError_t stage_bx(const dgb::BxArgs& A, unsigned grid, hipStream_t st);
+template <int N>
+hipError_t stage_bx_r(const dgb::BxArgs& A, unsigned grid, hipStream_t st);
+template <int N>
+hipError_t stage_bx_d(const dgb::BxArgsT<double>& A, unsigned grid, hipStream_t st);
+template <int N>
+hipError_t adj_tile(const dgt::TileArgs& A, unsigned grid, hipStream_t st);
+// orders 5-7: `grid` elements
+template <int N, bool F32>
+hipError_t stage_be(const dgb::BeArgs& A, unsigned grid, hipStream_t st);
+template <int N>
+hipError_t stage_be_d(const dgb::BeArgsT<double>& A, unsigned grid, hipStream_t st);
+// one stage of a batch of order N over `grid` launch positions
+template <int N, bool F32>
+hipError_t stage_batch(const dgb::BatchSlot* table, int n, unsigned grid, hipStream_t st, int par,
+                       float a, float b);
+
+}  // namespace dgl

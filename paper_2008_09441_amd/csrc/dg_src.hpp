@@ -57,14 +57,14 @@ namespace dgs {
 // count (stored as a double holding an exact integer, < 2^53).  Launches that
 // read it have arguments independent of the time, so a captured graph of a
 // run can be replayed at any time.
-__global__ void clock_set(double* clk, double t) {
+static __global__ void clock_set(double* clk, double t) {
   if (threadIdx.x == 0 && blockIdx.x == 0) {
     clk[0] = t;
     clk[1] = 0.0;
   }
 }
 
-__global__ void clock_advance(double* clk, double dt, int64_t nsteps) {
+static __global__ void clock_advance(double* clk, double dt, int64_t nsteps) {
   if (threadIdx.x == 0 && blockIdx.x == 0) {
     // t0 + n dt from the step count, not a running sum (no drift)
     clk[1] += double(nsteps);
