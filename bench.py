@@ -112,11 +112,13 @@ def parse():
 
 
 def stage_kernel_name(precision, N):
-    """The kernel one stage launches for this precision and order."""
+    """The kernel one stage of a large mesh launches for this precision and
+    order."""
     if precision == "bf16x3":
-        return f"stage_bx<{N}>" if N <= 4 else f"stage_be<{N}>"
+        return f"stage_bx<{N}>" if N <= 4 else f"stage_bt<{N},2>"
     if precision == "fp32":
-        return f"stage_bx<{N},f32>" if N <= 4 else f"stage_be<{N},f32>"
+        return (f"stage_bx<{N},f32>" if N <= 4 else
+                f"stage_bt<{N},3>" if N <= 6 else f"stage_be<{N},f32>")
     return f"stage_bx_d<{N}>" if N <= 4 else f"stage_be_d<{N}>"
 
 

@@ -75,7 +75,8 @@ struct dg_ctx {
   DevBuf fmask, geo, fgeo, etoe, etop, pat;
   DevBuf irho, lam, mu, zp, zs;
   DevBuf q[2], res;
-  DevBuf frags;             // BF16x3: operator hi/lo fragments
+  DevBuf frags;             // operator fragments of the matrix-core stages
+  DevBuf frags6;            // FP32, orders 5 and 6: the operators in three bf16 parts
   DevBuf matblk;            // BF16x3: material blocked by 16-element tile
   DevBuf nbn;               // BF16x3: neighbour volume node of each face node
   DevBuf torder;            // BF16x3: tile processed at each launch position
@@ -166,6 +167,16 @@ bool plain_material(int32_t precision, int order) {
 // kernels through launch_stage.
 bool tiled_mfma(const dg_ctx* c) {
   return c->opt.precision == DG_FP32_BF16X3 || c->opt.precision == DG_FP32;
+}
+// Orders 5-7 of BF16x3, 5 and 6 of FP32 (at order 7 the three parts of the
+// fluxes do not fit in LDS): 16-element tiles with the operator rows split over
+// the waves (stage_bt), from 72 tiles on.  A tile takes 22-48 us however few
+// there are, one element per workgroup (stage_be) 13-38 ns an element once the
+// chip is full: the two meet at 60-80 tiles at each of these orders.
+constexpr int64_t kRowTilesMin = 72;
+bool row_tiles(int32_t precision, int order, int64_t K) {
+  return order >= 5 && (precision == DG_FP32_BF16X3 || (precision == DG_FP32 && order <= 6)) &&
+         (K + dgb::kTile - 1) / dgb::kTile >= kRowTilesMin;
 }
 // FP32 contexts of orders 1-4 run the reverse stage on the tiled adjoint
 // kernel (matrix cores); the others on the generic adjoint kernels
@@ -355,14 +366,9 @@ hipError_t launch_mfma_n(dg_ctx* c, const float* q_in, float* q_out, float* res,
     return dgl::stage_bx<N, F32>(A, unsigned(tiles), c->stream);
 }
 
-template <int N, bool F32>
-hipError_t launch_mfma_e(dg_ctx* c, const float* q_in, float* q_out, float* res, float* rhs_out,
-                         double a, double b, double dt, int lsrk) {
-  dgb::BeArgs A;
-  A.q_in = q_in;
-  A.q_out = q_out;
-  A.res = res;
-  A.rhs_out = rhs_out;
+// arguments of the orders 5-7 stages that the context fixes
+dgb::BeArgs be_args(const dg_ctx* c) {
+  dgb::BeArgs A{};
   A.geo = static_cast<const float*>(c->geo.p);
   A.fgeo = static_cast<const float*>(c->fgeo.p);
   A.nbn = static_cast<const int32_t*>(c->nbn.p);
@@ -372,15 +378,30 @@ hipError_t launch_mfma_e(dg_ctx* c, const float* q_in, float* q_out, float* res,
   A.mu = static_cast<const float*>(c->mu.p);
   A.zp = static_cast<const float*>(c->zp.p);
   A.zs = static_cast<const float*>(c->zs.p);
-  A.frags = static_cast<const dgb::u32x4*>(c->frags.p);
+  const bool six = c->opt.precision == DG_FP32 &&
+                   row_tiles(c->opt.precision, c->re.N, c->mesh.K);
+  A.frags = static_cast<const dgb::u32x4*>(six ? c->frags6.p : c->frags.p);
   A.K = c->mesh.K;
+  A.upwind = c->opt.flux == DG_FLUX_UPWIND ? 1 : 0;
+  return A;
+}
+
+template <int N, bool F32>
+hipError_t launch_mfma_e(dg_ctx* c, const float* q_in, float* q_out, float* res, float* rhs_out,
+                         double a, double b, double dt, int lsrk) {
+  dgb::BeArgs A = be_args(c);
+  A.q_in = q_in;
+  A.q_out = q_out;
+  A.res = res;
+  A.rhs_out = rhs_out;
   A.a = float(a);
   A.b = float(b);
   A.dt = float(dt);
   A.lsrk = lsrk;
-  A.upwind = c->opt.flux == DG_FLUX_UPWIND ? 1 : 0;
-  // one workgroup per element
   if (c->mesh.K > 0x7fffffff) return hipErrorInvalidValue;
+  if (row_tiles(c->opt.precision, N, c->mesh.K))
+    return dgl::stage_bt<N, F32>(A, unsigned((c->mesh.K + dgb::kTile - 1) / dgb::kTile), c->stream);
+  // one workgroup per element
   return dgl::stage_be<N, F32>(A, unsigned(c->mesh.K), c->stream);
 }
 
@@ -1035,13 +1056,15 @@ dg_status exception_status() {
 // arguments, then each step runs five stage launches, five source launches
 // and one receiver launch for the whole batch.
 
-hipError_t batch_stage(int N, bool f32, const dgb::BatchSlot* table, int n, int64_t grid,
-                       hipStream_t st, int par, double a, double b) {
+hipError_t batch_stage(int N, bool f32, bool tiles, const dgb::BatchSlot* table, int n,
+                       int64_t grid, hipStream_t st, int par, double a, double b) {
   switch (N) {
-#define DG_BATCH_CASE(NN)                                                                  \
-  case NN:                                                                                 \
-    return f32 ? dgl::stage_batch<NN, true>(table, n, unsigned(grid), st, par, float(a), float(b)) \
-               : dgl::stage_batch<NN, false>(table, n, unsigned(grid), st, par, float(a), float(b));
+#define DG_BATCH_CASE(NN)                                                                     \
+  case NN:                                                                                    \
+    return f32 ? dgl::stage_batch<NN, true>(table, n, unsigned(grid), tiles, st, par, float(a), \
+                                            float(b))                                         \
+               : dgl::stage_batch<NN, false>(table, n, unsigned(grid), tiles, st, par, float(a), \
+                                             float(b));
     DG_BATCH_CASE(1)
     DG_BATCH_CASE(2)
     DG_BATCH_CASE(3)
@@ -1052,6 +1075,12 @@ hipError_t batch_stage(int N, bool f32, const dgb::BatchSlot* table, int n, int6
 #undef DG_BATCH_CASE
     default: return hipErrorInvalidValue;
   }
+}
+
+// whether a context's stage runs on element tiles or on one element per
+// workgroup, alone and in a batch
+bool batch_tiled(const dg_ctx* c) {
+  return c->re.N <= 4 || row_tiles(c->opt.precision, c->re.N, c->mesh.K);
 }
 
 // the slot of context c (state buffers in the order of its current parity)
@@ -1084,25 +1113,13 @@ dgb::BatchSlot batch_slot_of(const dg_ctx* c, double dt, int64_t first) {
     S.nwg = (c->mesh.K + dgb::kTile - 1) / dgb::kTile;
   } else {
     dgb::BeArgs& A = S.k.be;
+    A = be_args(c);
     A.q_in = q0;
     A.q_out = q1;
     A.res = res;
-    A.rhs_out = nullptr;
-    A.geo = static_cast<const float*>(c->geo.p);
-    A.fgeo = static_cast<const float*>(c->fgeo.p);
-    A.nbn = static_cast<const int32_t*>(c->nbn.p);
-    A.fmask = static_cast<const int32_t*>(c->fmask.p);
-    A.irho = static_cast<const float*>(c->irho.p);
-    A.lam = static_cast<const float*>(c->lam.p);
-    A.mu = static_cast<const float*>(c->mu.p);
-    A.zp = static_cast<const float*>(c->zp.p);
-    A.zs = static_cast<const float*>(c->zs.p);
-    A.frags = static_cast<const dgb::u32x4*>(c->frags.p);
-    A.K = c->mesh.K;
     A.dt = float(dt);
     A.lsrk = 1;
-    A.upwind = c->opt.flux == DG_FLUX_UPWIND ? 1 : 0;
-    S.nwg = c->mesh.K;
+    S.nwg = batch_tiled(c) ? (c->mesh.K + dgb::kTile - 1) / dgb::kTile : c->mesh.K;
   }
   S.first = first;
   S.q[0] = q0;
@@ -1154,18 +1171,25 @@ dg_status batch_advance_impl(void* table, dgb::BatchSlot* slots, int max_slots, 
   dg_status s = set_device(c0);
   if (s != DG_OK) return s;
   hipStream_t st = stream ? static_cast<hipStream_t>(stream) : c0->stream;
-  int64_t pos = 0;
+  // the slots of each stage kernel together (0: one element per workgroup, 1:
+  // tiles), with launch positions of their own
+  int64_t pos[2] = {0, 0};
+  int cnt[2] = {0, 0};
   bool any_src = false, any_rec = false;
   int max_np3 = 0, max_rec3 = 0;
-  for (int i = 0; i < n; ++i) {
-    slots[i] = batch_slot_of(cs[i], dt[i], pos);
-    pos += (slots[i].nwg + 7) / 8 * 8;
-    any_src = any_src || slots[i].nsrc > 0;
-    any_rec = any_rec || (slots[i].nrec > 0 && slots[i].trace_cap > 0);
-    max_np3 = std::max(max_np3, 3 * slots[i].Np);
-    max_rec3 = std::max(max_rec3, 3 * slots[i].nrec);
-  }
-  if (pos > 0x7fffffff) return fail(c0, DG_EINVAL, "batch: too many workgroups for one grid");
+  for (int kind = 0, at = 0; kind < 2; ++kind)
+    for (int i = 0; i < n; ++i) {
+      if (int(batch_tiled(cs[i])) != kind) continue;
+      dgb::BatchSlot& S = slots[at++];
+      S = batch_slot_of(cs[i], dt[i], pos[kind]);
+      pos[kind] += (S.nwg + 7) / 8 * 8;
+      ++cnt[kind];
+      any_src = any_src || S.nsrc > 0;
+      any_rec = any_rec || (S.nrec > 0 && S.trace_cap > 0);
+      max_np3 = std::max(max_np3, 3 * S.Np);
+      max_rec3 = std::max(max_rec3, 3 * S.nrec);
+    }
+  if (pos[0] > 0x7fffffff || pos[1] > 0x7fffffff) return fail(c0, DG_EINVAL, "batch: too many workgroups for one grid");
   // the slot table, written by launches that carry it
   const size_t words = size_t(n) * sizeof(dgb::BatchSlot) / 4;
   static_assert(sizeof(dgb::BatchSlot) % 4 == 0, "whole words");
@@ -1185,7 +1209,12 @@ dg_status batch_advance_impl(void* table, dgb::BatchSlot* slots, int max_slots, 
   for (int64_t i = 0; i < nsteps; ++i) {
     for (int stg = 0; stg < 5; ++stg) {
       const int par = int((5 * i + stg) & 1);
-      const hipError_t e = batch_stage(c0->re.N, f32, tab, n, pos, st, par, kRkA[stg], kRkB[stg]);
+      hipError_t e = hipSuccess;
+      if (cnt[0] > 0)
+        e = batch_stage(c0->re.N, f32, false, tab, cnt[0], pos[0], st, par, kRkA[stg], kRkB[stg]);
+      if (e == hipSuccess && cnt[1] > 0)
+        e = batch_stage(c0->re.N, f32, true, tab + cnt[0], cnt[1], pos[1], st, par, kRkA[stg],
+                        kRkB[stg]);
       if (e != hipSuccess)
         return fail(c0, DG_EDEVICE, std::string("batch stage launch: ") + hipGetErrorString(e));
       if (any_src) {
@@ -1275,7 +1304,9 @@ dg_status dg_create(dg_ctx** out, const dg_options* opt) {
         }
       } else if (opt->precision == DG_FP32) {
         const std::vector<float> fr = dgh::mfma_fragments_f32(re);
-        if (upload_raw(c, c->frags, fr.data(), fr.size()) != DG_OK) {
+        const std::vector<uint16_t> fr6 = dgh::mfma_fragments_bf16x6(re);   // may be empty
+        if (upload_raw(c, c->frags, fr.data(), fr.size()) != DG_OK ||
+            (!fr6.empty() && upload_raw(c, c->frags6, fr6.data(), fr6.size()) != DG_OK)) {
           dg_destroy(c);
           return DG_ENOMEM;
         }
@@ -1306,7 +1337,7 @@ void dg_destroy(dg_ctx* c) {
     release(c, c->trace);
     for (DevBuf* b : {&c->ops, &c->opsT, &c->fmask, &c->geo, &c->fgeo, &c->etoe, &c->etop, &c->pat,
                       &c->irho, &c->lam, &c->mu, &c->zp, &c->zs, &c->q[0], &c->q[1],
-                      &c->res, &c->frags, &c->matblk, &c->nbn, &c->torder, &c->src_elem, &c->src_w,
+                      &c->res, &c->frags, &c->frags6, &c->matblk, &c->nbn, &c->torder, &c->src_elem, &c->src_w,
                       &c->src_par, &c->rec_elem, &c->rec_w, &c->rec_buf, &c->src_wraw,
                       &c->adj_nbface, &c->adj_invf, &c->adj_ck, &c->adj_seg, &c->adj_r,
                       &c->adj_j, &c->adj_v, &c->adj_gb, &c->adj_hb, &c->adj_grad, &c->adj_zb,
@@ -1904,7 +1935,9 @@ dg_status dg_footprint(int32_t order, int32_t precision, int64_t K, int32_t nsrc
     b += (3 * Np * NpP + NF4 * NpP + Np * QP + QP * NpP) * e;           // transposed operators
     b += NF4 * 4;                                                       // face masks
     if (precision == DG_FP32_BF16X3) b += uint64_t(dgh::mfma_frag_count(order)) * 64 * 8 * 2;
-    else if (precision == DG_FP32) b += uint64_t(dgh::mfma_f32_frag_count(order)) * 16;
+    else if (precision == DG_FP32)
+      b += uint64_t(dgh::mfma_f32_frag_count(order)) * 16 +
+           (order == 5 || order == 6 ? uint64_t(dgh::mfma_frag_count(order)) / 2 * 3 * 64 * 16 : 0);
     else b += uint64_t(dgh::mfma_f32_frag_count(order)) * 32;   // FP64 fragments
     b += k * (9 + 16) * e + k * 4 * 4 + k * 4 + 96 * Nfp * 4;          // geometry, tables
     b += 3 * 9 * k * Np * e + 2 * sizeof(double);                      // q[2], res, clock

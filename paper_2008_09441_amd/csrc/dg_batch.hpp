@@ -2,9 +2,9 @@
 // (FP32 or FP32 + BF16x3 state) by one launch per stage: the serving path's
 // continuous batching.  Every context is one slot of a table in device
 // memory; a slot owns a range of launch positions and runs the same stage
-// body as a single-context launch over its own tiles (orders 1-4) or
-// elements (orders 5-7), so each context's result is bit-identical alone and
-// in a batch.  Sources, receivers and the device clocks of all slots are
+// body as a single-context launch over its own element tiles or elements, so
+// each context's result is bit-identical alone and in a batch (a batch whose
+// contexts run on both kinds takes one launch for each).  Sources, receivers and the device clocks of all slots are
 // handled by one launch each as well.
 //
 // Buffer parity: slot s keeps its two state buffers as q[0] (the current
@@ -17,6 +17,7 @@
 #include <cstdint>
 
 #include "dg_be.hpp"
+#include "dg_bt.hpp"
 #include "dg_bx.hpp"
 
 namespace dgb {
@@ -28,7 +29,7 @@ struct BatchSlot {
   } k;
   int64_t first;         // first launch position (a multiple of 8, so that
                          // position p of the slot runs on the XCD p & 7)
-  int64_t nwg;           // launch positions: tiles (1-4) or elements (5-7)
+  int64_t nwg;           // launch positions: element tiles or elements
   float* q[2];
   float* res;
   int64_t KNp;
@@ -88,6 +89,22 @@ __global__ __launch_bounds__(kThreads, 2) void stage_be_batch(const BatchSlot* s
   A.a = a;
   A.b = b;
   stage_be_run<N, F32>(A, slots[s].nwg, p);
+}
+
+template <int N, int P>
+__global__ __launch_bounds__((TOrd<N, P>::TH), 2) void stage_bt_batch(const BatchSlot* slots,
+                                                                      int nslots, int par, float a,
+                                                                      float b) {
+  const int64_t bid = blockIdx.x;
+  const int s = batch_slot(slots, nslots, bid);
+  const int64_t p = bid - slots[s].first;
+  if (p >= slots[s].nwg) return;
+  BeArgs A = slots[s].k.be;
+  A.q_in = slots[s].q[par];
+  A.q_out = slots[s].q[1 - par];
+  A.a = a;
+  A.b = b;
+  stage_bt_run<N, P>(A, slots[s].nwg, p);
 }
 
 // After stage st of step i (parity par): res += dt f(t) w and

@@ -94,6 +94,13 @@ __device__ __forceinline__ void be_bread(const float* buf, int s, int g, int e, 
   for (int j = 0; j < 8; ++j) v[j] = buf[(32 * s + 8 * g + j) * kCS + e];
 }
 
+// the same in the K order of the P_q fragments (EOrd): rows 32 s + 16 (j / 4) +
+// 4 g + j % 4
+__device__ __forceinline__ void be_bread_p(const float* buf, int s, int g, int e, float (&v)[8]) {
+#pragma unroll
+  for (int j = 0; j < 8; ++j) v[j] = buf[(32 * s + 16 * (j / 4) + 4 * g + j % 4) * kCS + e];
+}
+
 __device__ __forceinline__ void be_fload(const BeArgs& A, int frag, int lane, u32x4& ah,
                                          u32x4& al) {
   ah = A.frags[(frag + 0) * 64 + lane];
@@ -476,7 +483,7 @@ __device__ __forceinline__ void stage_be_run(const BeArgsT<T>& A, int64_t Gd, in
     else
       be_pipe<KQ, TW>(
           A, lane, [&](int s, int i) { return O::OFF_P + (tn[i] * KQ + s) * 2; },
-          [&](int s, T(&v)[8]) { be_bread(sw, s, g, e, v); }, acc);
+          [&](int s, T(&v)[8]) { be_bread_p(sw, s, g, e, v); }, acc);
 #pragma unroll
     for (int i = 0; i < TW; ++i) {
       const int t = wave + 4 * i;

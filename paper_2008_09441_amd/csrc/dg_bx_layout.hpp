@@ -57,11 +57,12 @@ struct BOrd {
 
 namespace dgb {
 
-// Sizes and fragment offsets of the BF16x3 stage for orders 5-7, which
-// works on one element per workgroup with the nine fields (or output
-// components) as the MFMA columns.  Operator fragments are in plain K order:
-// fragment (t, s) holds, for lane l, rows 16 t + l % 16 and K slots
-// 32 s + 8 (l / 16) + j (j < 8) of the operator, hi and lo adjacent.
+// Sizes and fragment offsets of the split-product stages for orders 5-7: one
+// element per workgroup with the nine fields (or output components) as the
+// MFMA columns, or 16-element tiles.  Fragment (t, s) holds, for lane l, row
+// 16 t + l % 16 and columns 32 s + 8 (l / 16) + j (j < 8) of the operator, of
+// P_q columns 32 s + 16 (j / 4) + 4 (l / 16) + j % 4 (the accumulator rows of
+// quadrature tiles 2 s and 2 s + 1), its parts (hi, lo) adjacent.
 template <int N>
 struct EOrd {
   static constexpr int Np = (N + 1) * (N + 2) * (N + 3) / 6;

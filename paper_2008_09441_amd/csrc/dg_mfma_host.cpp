@@ -119,21 +119,26 @@ std::vector<V> build_frags_f(const RefElement& re) {
   return out;
 }
 
-// Fragments of the high-order stage (EOrd): D_r, D_s, D_t, LIFT, V_q, P_q in
-// plain K order, zero beyond the operator's rows and columns
-template <int N>
+// Fragments of the high-order stages (EOrd): D_r, D_s, D_t, LIFT, V_q in plain
+// K order and P_q in the order of the accumulator rows, P bf16 parts each (the
+// operator entry to 8 P bits), zero beyond the operator's rows and columns
+template <int N, int P>
 std::vector<uint16_t> build_frags_e(const RefElement& re) {
   using O = dgb::EOrd<N>;
-  std::vector<uint16_t> out(size_t(O::NFRAG) * 64 * 8, 0);
-  auto put = [&](int frag, const std::vector<double>& M, int rows, int cols, int t, int s) {
+  std::vector<uint16_t> out(size_t(O::NFRAG) / 2 * P * 64 * 8, 0);
+  auto put = [&](int frag, const std::vector<double>& M, int rows, int cols, int t, int s,
+                 bool acc) {
     for (int l = 0; l < 64; ++l)
       for (int j = 0; j < 8; ++j) {
-        const int r = 16 * t + l % 16, k = 32 * s + 8 * (l / 16) + j;
-        const double v = (r < rows && k < cols) ? M[size_t(r) * cols + k] : 0.0;
-        const uint16_t hi = bf16_rne(float(v));
-        const uint16_t lo = bf16_rne(float(v - double(bf16_val(hi))));
-        out[(size_t(frag) * 64 + l) * 8 + j] = hi;
-        out[(size_t(frag + 1) * 64 + l) * 8 + j] = lo;
+        const int g = l / 16;
+        const int r = 16 * t + l % 16;
+        const int k = 32 * s + (acc ? 16 * (j / 4) + 4 * g + j % 4 : 8 * g + j);
+        double v = (r < rows && k < cols) ? M[size_t(r) * cols + k] : 0.0;
+        for (int p = 0; p < P; ++p) {
+          const uint16_t h = bf16_rne(float(v));
+          out[(size_t(frag / 2 * P + p) * 64 + l) * 8 + j] = h;
+          v -= double(bf16_val(h));
+        }
       }
   };
   const int Np = O::Np, NF4 = O::NF4, Nq = O::Nq;
@@ -141,13 +146,16 @@ std::vector<uint16_t> build_frags_e(const RefElement& re) {
   for (int d = 0; d < 3; ++d)
     for (int t = 0; t < O::RT; ++t)
       for (int s = 0; s < O::KN; ++s)
-        put(O::OFF_D + ((d * O::RT + t) * O::KN + s) * 2, *D[d], Np, Np, t, s);
+        put(O::OFF_D + ((d * O::RT + t) * O::KN + s) * 2, *D[d], Np, Np, t, s, false);
   for (int t = 0; t < O::RT; ++t)
-    for (int s = 0; s < O::KF; ++s) put(O::OFF_L + (t * O::KF + s) * 2, re.LIFT, Np, NF4, t, s);
+    for (int s = 0; s < O::KF; ++s)
+      put(O::OFF_L + (t * O::KF + s) * 2, re.LIFT, Np, NF4, t, s, false);
   for (int t = 0; t < O::QT; ++t)
-    for (int s = 0; s < O::KN; ++s) put(O::OFF_V + (t * O::KN + s) * 2, re.Vq, Nq, Np, t, s);
+    for (int s = 0; s < O::KN; ++s)
+      put(O::OFF_V + (t * O::KN + s) * 2, re.Vq, Nq, Np, t, s, false);
   for (int t = 0; t < O::RT; ++t)
-    for (int s = 0; s < O::KQ; ++s) put(O::OFF_P + (t * O::KQ + s) * 2, re.Pq, Np, Nq, t, s);
+    for (int s = 0; s < O::KQ; ++s)
+      put(O::OFF_P + (t * O::KQ + s) * 2, re.Pq, Np, Nq, t, s, true);
   return out;
 }
 
@@ -186,9 +194,17 @@ std::vector<uint16_t> mfma_fragments(const RefElement& re) {
     case 2: return build_frags<2>(re);
     case 3: return build_frags<3>(re);
     case 4: return build_frags<4>(re);
-    case 5: return build_frags_e<5>(re);
-    case 6: return build_frags_e<6>(re);
-    default: return build_frags_e<7>(re);
+    case 5: return build_frags_e<5, 2>(re);
+    case 6: return build_frags_e<6, 2>(re);
+    default: return build_frags_e<7, 2>(re);
+  }
+}
+
+std::vector<uint16_t> mfma_fragments_bf16x6(const RefElement& re) {
+  switch (re.N) {
+    case 5: return build_frags_e<5, 3>(re);
+    case 6: return build_frags_e<6, 3>(re);
+    default: return {};
   }
 }
 

@@ -18,6 +18,11 @@ bool mfma_supported(int N);
 // lanes][8]
 std::vector<uint16_t> mfma_fragments(const RefElement& re);
 
+// the same operators in three bf16 parts, in the layout of the BF16x3
+// fragments of orders 5-7 with three parts per fragment: the FP32 stage on
+// 16-element tiles (orders 5 and 6; empty at the others)
+std::vector<uint16_t> mfma_fragments_bf16x6(const RefElement& re);
+
 // FP32 operator fragments of the FP32 matrix-core stage: orders 1-4 in the
 // layout of FOrd ([NF4S][4] floats), orders 5-7 in that of EFOrd
 // ([NFRAG][64 lanes][4] floats)

@@ -38,6 +38,17 @@ hipError_t stage_be(const dgb::BeArgs& A, unsigned grid, hipStream_t st) {
   return hipGetLastError();
 }
 
+template <int N, bool F32>
+hipError_t stage_bt(const dgb::BeArgs& A, unsigned grid, hipStream_t st) {
+  if constexpr (F32 && N > 6) {
+    return hipErrorInvalidValue;
+  } else {
+    constexpr int P = F32 ? 3 : 2;
+    dgb::stage_bt<N, P><<<dim3(grid), dim3(dgb::TOrd<N, P>::TH), 0, st>>>(A);
+    return hipGetLastError();
+  }
+}
+
 template <int N>
 hipError_t stage_be_d(const dgb::BeArgsT<double>& A, unsigned grid, hipStream_t st) {
   dgb::stage_be_d<N><<<dim3(grid), dim3(dgb::kThreads), 0, st>>>(A);
@@ -45,12 +56,20 @@ hipError_t stage_be_d(const dgb::BeArgsT<double>& A, unsigned grid, hipStream_t 
 }
 
 template <int N, bool F32>
-hipError_t stage_batch(const dgb::BatchSlot* table, int n, unsigned grid, hipStream_t st, int par,
-                       float a, float b) {
-  if constexpr (N <= 4)
+hipError_t stage_batch(const dgb::BatchSlot* table, int n, unsigned grid, bool tiles,
+                       hipStream_t st, int par, float a, float b) {
+  if constexpr (N <= 4) {
+    if (!tiles) return hipErrorInvalidValue;
     dgb::stage_bx_batch<N, F32><<<dim3(grid), dim3(dgb::kThreads), 0, st>>>(table, n, par, a, b);
-  else
+  } else if (!tiles) {
     dgb::stage_be_batch<N, F32><<<dim3(grid), dim3(dgb::kThreads), 0, st>>>(table, n, par, a, b);
+  } else if constexpr (F32 && N > 6) {
+    return hipErrorInvalidValue;
+  } else {
+    constexpr int P = F32 ? 3 : 2;
+    dgb::stage_bt_batch<N, P>
+        <<<dim3(grid), dim3(dgb::TOrd<N, P>::TH), 0, st>>>(table, n, par, a, b);
+  }
   return hipGetLastError();
 }
 
@@ -58,8 +77,8 @@ hipError_t stage_batch(const dgb::BatchSlot* table, int n, unsigned grid, hipStr
 // adjoint and its replay stage
 #define DG_INST template hipError_t
 #if DG_PART < 2
-DG_INST stage_batch<DG_ORDER, DG_PART == 1>(const dgb::BatchSlot*, int, unsigned, hipStream_t, int,
-                                            float, float);
+DG_INST stage_batch<DG_ORDER, DG_PART == 1>(const dgb::BatchSlot*, int, unsigned, bool, hipStream_t,
+                                            int, float, float);
 #endif
 #if DG_ORDER <= 4
 #if DG_PART < 2
@@ -73,6 +92,7 @@ DG_INST adj_tile<DG_ORDER>(const dgt::TileArgs&, unsigned, hipStream_t);
 #else
 #if DG_PART < 2
 DG_INST stage_be<DG_ORDER, DG_PART == 1>(const dgb::BeArgs&, unsigned, hipStream_t);
+DG_INST stage_bt<DG_ORDER, DG_PART == 1>(const dgb::BeArgs&, unsigned, hipStream_t);
 #elif DG_PART == 2
 DG_INST stage_be_d<DG_ORDER>(const dgb::BeArgsT<double>&, unsigned, hipStream_t);
 #endif

@@ -16,9 +16,9 @@
 thread_local emu_dim3 threadIdx, blockIdx;
 emu_dim3 gridDim, blockDim;
 static std::unique_ptr<std::barrier<>> g_bar;
-static std::unique_ptr<std::barrier<>> g_wbar[4];
+static std::unique_ptr<std::barrier<>> g_wbar[8];   // up to eight waves
 struct Slot { emu_bf16x8 a[64], b[64]; float x[64], fa[64], fb[64]; double da[64], db[64], xd[64]; };
-static Slot g_slot[4];
+static Slot g_slot[8];
 
 void __syncthreads() { g_bar->arrive_and_wait(); }
 
@@ -102,13 +102,13 @@ emu_f64x4 emu_mfma_16x16x4_f64(double a, double b, emu_f64x4 c, int, int, int) {
 }
 
 template <typename F>
-static void run_grid(int grid, F kern) {
-  gridDim.x = grid; blockDim.x = 256;
+static void run_grid(int grid, F kern, int threads = 256) {
+  gridDim.x = grid; blockDim.x = threads;
   for (int b = 0; b < grid; ++b) {
-    g_bar = std::make_unique<std::barrier<>>(256);
-    for (int w = 0; w < 4; ++w) g_wbar[w] = std::make_unique<std::barrier<>>(64);
+    g_bar = std::make_unique<std::barrier<>>(threads);
+    for (int w = 0; w < threads / 64; ++w) g_wbar[w] = std::make_unique<std::barrier<>>(64);
     std::vector<std::thread> th;
-    for (int t = 0; t < 256; ++t)
+    for (int t = 0; t < threads; ++t)
       th.emplace_back([=]() { threadIdx.x = t; blockIdx.x = b; kern(); });
     for (auto& x : th) x.join();
   }

@@ -15,6 +15,7 @@
 #include <cstdlib>
 #include <cmath>
 #include "dg_be.hpp"
+#include "dg_bt.hpp"
 #include "dg_bx.hpp"
 #include "dg_host.hpp"
 #include "dg_mfma_host.hpp"
@@ -42,7 +43,7 @@ static int emu_rhs(int N, int64_t K, const double* vxyz, const double* period,
     d[i] = rho_q[i] * cs_q[i] * cs_q[i];
   }
   for (int64_t i = 0; i < K * Np; ++i) { zp[i] = rho_n[i] * cp_n[i]; zs[i] = rho_n[i] * cs_n[i]; }
-  if (grid < 1 || grid > 4) return 3;
+  if (grid < 1 || grid > 6) return 3;
   if (grid == 3 && N >= 5) {   // FP64 matrix-core kernel, orders 5-7
     dgb::BeArgsT<double> E{};
     std::vector<double> qd(q, q + 9 * K * Np);
@@ -120,7 +121,19 @@ static int emu_rhs(int N, int64_t K, const double* vxyz, const double* period,
       E.frags = reinterpret_cast<const dgb::u32x4*>(dup(fr));
     }
     E.K = K; E.a = 0.f; E.b = 1.f; E.dt = 1.f; E.lsrk = lsrk; E.upwind = upwind;
-    switch (N) {
+    const int tg = int((K + dgb::kTile - 1) / dgb::kTile);
+    if (grid == 6) {   // the same in three bf16 parts (FP32), orders 5 and 6
+      E.frags = reinterpret_cast<const dgb::u32x4*>(dup(dgh::mfma_fragments_bf16x6(re)));
+      if (N == 5) run_grid(tg, [=]() { dgb::stage_bt<5, 3>(E); }, dgb::TOrd<5, 3>::TH);
+      else if (N == 6) run_grid(tg, [=]() { dgb::stage_bt<6, 3>(E); }, dgb::TOrd<6, 3>::TH);
+      else return 3;
+    } else if (grid == 5) {   // 16-element tiles, operator rows split over the waves
+      switch (N) {
+        case 5: run_grid(tg, [=]() { dgb::stage_bt<5, 2>(E); }, dgb::TOrd<5, 2>::TH); break;
+        case 6: run_grid(tg, [=]() { dgb::stage_bt<6, 2>(E); }, dgb::TOrd<6, 2>::TH); break;
+        default: run_grid(tg, [=]() { dgb::stage_bt<7, 2>(E); }, dgb::TOrd<7, 2>::TH); break;
+      }
+    } else switch (N) {
       case 5: fe ? run_grid(int(K), [=]() { dgb::stage_be<5, true>(E); })
                  : run_grid(int(K), [=]() { dgb::stage_be<5, false>(E); }); break;
       case 6: fe ? run_grid(int(K), [=]() { dgb::stage_be<6, true>(E); })

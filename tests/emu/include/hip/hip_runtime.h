@@ -46,3 +46,15 @@ float emu_shfl(float v, int src, int width);
 double emu_shfl_d(double v, int src, int width);
 inline float __shfl(float v, int src, int width = 64) { return emu_shfl(v, src, width); }
 inline double __shfl(double v, int src, int width = 64) { return emu_shfl_d(v, src, width); }
+// raw buffer loads: a byte range, checked (ASan reports what the hardware's
+// bounds check would turn into zeros)
+struct emu_buffer_rsrc { const char* p; int n; };
+#define __amdgpu_buffer_rsrc_t emu_buffer_rsrc
+typedef unsigned emu_u32x4 __attribute__((ext_vector_type(4)));
+#define __builtin_amdgcn_make_buffer_rsrc(ptr, stride, bytes, flags) \
+  emu_buffer_rsrc{reinterpret_cast<const char*>(ptr), int(bytes)}
+inline emu_u32x4 emu_buffer_load_b128(emu_buffer_rsrc r, int voff, int soff, int) {
+  if (voff + soff < 0 || voff + soff + 16 > r.n) std::abort();
+  return *reinterpret_cast<const emu_u32x4*>(r.p + voff + soff);
+}
+#define __builtin_amdgcn_raw_buffer_load_b128 emu_buffer_load_b128
