@@ -76,6 +76,7 @@ struct dg_ctx {
   DevBuf irho, lam, mu, zp, zs;
   DevBuf q[2], res;
   DevBuf frags;             // operator fragments of the matrix-core stages
+  DevBuf efrags;            // orders 1-4: those of one element per workgroup
   DevBuf frags6;            // FP32, orders 5 and 6: the operators in three bf16 parts
   DevBuf matblk;            // BF16x3: material blocked by 16-element tile
   DevBuf nbn;               // BF16x3: neighbour volume node of each face node
@@ -154,13 +155,10 @@ bool device_ctx(const dg_ctx* c) { return c->opt.device >= 0; }
 // orders 1-4 (BF16x3, FP32 and FP64 products); it reads the blocked
 // material, the neighbour-node table and the tile order.  The [K][Nq]
 // material is held by every other context and by FP32 and FP64 ones too
-// (adjoint, sources).
+// (adjoint, sources) and by those that run one element per workgroup.
 bool tiled_kernel(int32_t precision, int order) {
   return order <= 4 &&
          (precision == DG_FP32_BF16X3 || precision == DG_FP32 || precision == DG_FP64);
-}
-bool plain_material(int32_t precision, int order) {
-  return !(precision == DG_FP32_BF16X3 && order <= 4);
 }
 // FP32 and BF16x3 contexts (launch_mfma: the tiled kernel at orders 1-4, one
 // element per workgroup at 5-7); FP64 contexts run the FP64 matrix-core
@@ -168,15 +166,24 @@ bool plain_material(int32_t precision, int order) {
 bool tiled_mfma(const dg_ctx* c) {
   return c->opt.precision == DG_FP32_BF16X3 || c->opt.precision == DG_FP32;
 }
-// Orders 5-7 of BF16x3, 5 and 6 of FP32 (at order 7 the three parts of the
-// fluxes do not fit in LDS): 16-element tiles with the operator rows split over
-// the waves (stage_bt), from 72 tiles on.  A tile takes 22-48 us however few
-// there are, one element per workgroup (stage_be) 13-38 ns an element once the
-// chip is full: the two meet at 60-80 tiles at each of these orders.
-constexpr int64_t kRowTilesMin = 72;
-bool row_tiles(int32_t precision, int order, int64_t K) {
-  return order >= 5 && (precision == DG_FP32_BF16X3 || (precision == DG_FP32 && order <= 6)) &&
-         (K + dgb::kTile - 1) / dgb::kTile >= kRowTilesMin;
+// Contexts of few 16-element tiles run one element per workgroup (dg_be.hpp) at
+// orders 2-7: a tile takes its whole latency however few there are and leaves
+// the other CUs idle, one element per workgroup spreads over the chip but reads
+// every operator for each element.  us per stage on both sides (tiles,
+// elements): order 2 FP32 7.0, 6.3 at 384 elements and 7.3, 7.5 at 750; order 3
+// FP64 18.4, 11.1 at 384 and 18.9, 25.0 at 1,296, BF16x3 9.3, 7.7 at 750; order
+// 4 FP64 39, 21 at 750 and 41, 52 at 2,058, BF16x3 14.6, 10.2 at 750 and 14.8,
+// 17.7 at 1,296; orders 5-7 22-48 a tile against 13-38 ns an element.  At order
+// 1 tiles are never slower.  FP64 at orders 5-7 and FP32 at order 7 have no
+// tiled kernel (a tile's data does not fit in LDS).
+bool one_element(int32_t precision, int order, int64_t K) {
+  if (order >= 5 && (precision == DG_FP64 || (precision == DG_FP32 && order == 7))) return true;
+  const int64_t least[8] = {0, 0, 24, 48, 64, 72, 72, 72};   // tiles, by order
+  return (K + dgb::kTile - 1) / dgb::kTile < least[order];
+}
+bool one_element(const dg_ctx* c) { return one_element(c->opt.precision, c->re.N, c->mesh.K); }
+bool plain_material(int32_t precision, int order, int64_t K) {
+  return !(precision == DG_FP32_BF16X3 && order <= 4) || one_element(precision, order, K);
 }
 // FP32 contexts of orders 1-4 run the reverse stage on the tiled adjoint
 // kernel (matrix cores); the others on the generic adjoint kernels
@@ -274,32 +281,42 @@ hipError_t launch_mfma_d(const dg_ctx* c, const double* q_in, double* q_out, dou
   return dgl::stage_bx_d<N>(A, unsigned(tiles), c->stream);
 }
 
-// FP64 stage on the matrix cores at orders 5-7: one element per workgroup
+// arguments of the one-element stages and the orders 5-7 tiles that the context
+// fixes
+template <typename T>
+dgb::BeArgsT<T> be_args(const dg_ctx* c) {
+  dgb::BeArgsT<T> A{};
+  A.geo = static_cast<const T*>(c->geo.p);
+  A.fgeo = static_cast<const T*>(c->fgeo.p);
+  A.nbn = static_cast<const int32_t*>(c->nbn.p);
+  A.fmask = static_cast<const int32_t*>(c->fmask.p);
+  A.irho = static_cast<const T*>(c->irho.p);
+  A.lam = static_cast<const T*>(c->lam.p);
+  A.mu = static_cast<const T*>(c->mu.p);
+  A.zp = static_cast<const T*>(c->zp.p);
+  A.zs = static_cast<const T*>(c->zs.p);
+  A.frags = static_cast<const dgb::u32x4*>(
+      c->re.N <= 4 ? c->efrags.p
+      : c->opt.precision == DG_FP32 && !one_element(c) ? c->frags6.p : c->frags.p);
+  A.K = c->mesh.K;
+  A.upwind = c->opt.flux == DG_FLUX_UPWIND ? 1 : 0;
+  return A;
+}
+
+// FP64 stage on the matrix cores: one element per workgroup
 // with FP64 fragments and v_mfma_f64_16x16x4f64 (dg_be.hpp)
 template <int N>
 hipError_t launch_be_d(const dg_ctx* c, const double* q_in, double* q_out, double* res,
                        double* rhs_out, double a, double b, double dt, int lsrk) {
-  dgb::BeArgsT<double> A;
+  dgb::BeArgsT<double> A = be_args<double>(c);
   A.q_in = q_in;
   A.q_out = q_out;
   A.res = res;
   A.rhs_out = rhs_out;
-  A.geo = static_cast<const double*>(c->geo.p);
-  A.fgeo = static_cast<const double*>(c->fgeo.p);
-  A.nbn = static_cast<const int32_t*>(c->nbn.p);
-  A.fmask = static_cast<const int32_t*>(c->fmask.p);
-  A.irho = static_cast<const double*>(c->irho.p);
-  A.lam = static_cast<const double*>(c->lam.p);
-  A.mu = static_cast<const double*>(c->mu.p);
-  A.zp = static_cast<const double*>(c->zp.p);
-  A.zs = static_cast<const double*>(c->zs.p);
-  A.frags = static_cast<const dgb::u32x4*>(c->frags.p);
-  A.K = c->mesh.K;
   A.a = a;
   A.b = b;
   A.dt = dt;
   A.lsrk = lsrk;
-  A.upwind = c->opt.flux == DG_FLUX_UPWIND ? 1 : 0;
   if (c->mesh.K > 0x7fffffff) return hipErrorInvalidValue;
   return dgl::stage_be_d<N>(A, unsigned(c->mesh.K), c->stream);
 }
@@ -309,6 +326,13 @@ hipError_t launch_be_d(const dg_ctx* c, const double* q_in, double* q_out, doubl
 // BF16x3 contexts run on the matrix cores at every order (launch_mfma)
 hipError_t launch_stage_f64(const dg_ctx* c, const double* q_in, double* q_out, double* res,
                             double* rhs_out, double a, double b, double dt, int lsrk) {
+  if (c->re.N <= 4 && one_element(c)) {
+    switch (c->re.N) {
+      case 2: return launch_be_d<2>(c, q_in, q_out, res, rhs_out, a, b, dt, lsrk);
+      case 3: return launch_be_d<3>(c, q_in, q_out, res, rhs_out, a, b, dt, lsrk);
+      default: return launch_be_d<4>(c, q_in, q_out, res, rhs_out, a, b, dt, lsrk);
+    }
+  }
   switch (c->re.N) {
     case 1: return launch_mfma_d<1>(c, q_in, q_out, res, rhs_out, a, b, dt, lsrk);
     case 2: return launch_mfma_d<2>(c, q_in, q_out, res, rhs_out, a, b, dt, lsrk);
@@ -366,30 +390,10 @@ hipError_t launch_mfma_n(dg_ctx* c, const float* q_in, float* q_out, float* res,
     return dgl::stage_bx<N, F32>(A, unsigned(tiles), c->stream);
 }
 
-// arguments of the orders 5-7 stages that the context fixes
-dgb::BeArgs be_args(const dg_ctx* c) {
-  dgb::BeArgs A{};
-  A.geo = static_cast<const float*>(c->geo.p);
-  A.fgeo = static_cast<const float*>(c->fgeo.p);
-  A.nbn = static_cast<const int32_t*>(c->nbn.p);
-  A.fmask = static_cast<const int32_t*>(c->fmask.p);
-  A.irho = static_cast<const float*>(c->irho.p);
-  A.lam = static_cast<const float*>(c->lam.p);
-  A.mu = static_cast<const float*>(c->mu.p);
-  A.zp = static_cast<const float*>(c->zp.p);
-  A.zs = static_cast<const float*>(c->zs.p);
-  const bool six = c->opt.precision == DG_FP32 &&
-                   row_tiles(c->opt.precision, c->re.N, c->mesh.K);
-  A.frags = static_cast<const dgb::u32x4*>(six ? c->frags6.p : c->frags.p);
-  A.K = c->mesh.K;
-  A.upwind = c->opt.flux == DG_FLUX_UPWIND ? 1 : 0;
-  return A;
-}
-
 template <int N, bool F32>
 hipError_t launch_mfma_e(dg_ctx* c, const float* q_in, float* q_out, float* res, float* rhs_out,
                          double a, double b, double dt, int lsrk) {
-  dgb::BeArgs A = be_args(c);
+  dgb::BeArgs A = be_args<float>(c);
   A.q_in = q_in;
   A.q_out = q_out;
   A.res = res;
@@ -399,8 +403,13 @@ hipError_t launch_mfma_e(dg_ctx* c, const float* q_in, float* q_out, float* res,
   A.dt = float(dt);
   A.lsrk = lsrk;
   if (c->mesh.K > 0x7fffffff) return hipErrorInvalidValue;
-  if (row_tiles(c->opt.precision, N, c->mesh.K))
-    return dgl::stage_bt<N, F32>(A, unsigned((c->mesh.K + dgb::kTile - 1) / dgb::kTile), c->stream);
+  if (!one_element(c)) {
+    if constexpr (N >= 5)
+      return dgl::stage_bt<N, F32>(A, unsigned((c->mesh.K + dgb::kTile - 1) / dgb::kTile),
+                                   c->stream);
+    else
+      return hipErrorInvalidValue;   // orders 1-4: launch_mfma_n
+  }
   // one workgroup per element
   return dgl::stage_be<N, F32>(A, unsigned(c->mesh.K), c->stream);
 }
@@ -413,6 +422,19 @@ dg_status launch_mfma(dg_ctx* c, const void* q_in, void* q_out, void* res, void*
   float* ro = static_cast<float*>(rhs_out);
   hipError_t e;
   const bool f32 = c->opt.precision == DG_FP32;
+  if (c->re.N <= 4 && one_element(c)) {
+    switch (c->re.N) {
+      case 2: e = f32 ? launch_mfma_e<2, true>(c, qi, qo, rs, ro, a, b, dt, lsrk)
+                      : launch_mfma_e<2, false>(c, qi, qo, rs, ro, a, b, dt, lsrk); break;
+      case 3: e = f32 ? launch_mfma_e<3, true>(c, qi, qo, rs, ro, a, b, dt, lsrk)
+                      : launch_mfma_e<3, false>(c, qi, qo, rs, ro, a, b, dt, lsrk); break;
+      default: e = f32 ? launch_mfma_e<4, true>(c, qi, qo, rs, ro, a, b, dt, lsrk)
+                       : launch_mfma_e<4, false>(c, qi, qo, rs, ro, a, b, dt, lsrk); break;
+    }
+    if (e != hipSuccess)
+      return fail(c, DG_EDEVICE, std::string("matrix-core stage launch: ") + hipGetErrorString(e));
+    return DG_OK;
+  }
   switch (c->re.N) {
     case 1: e = f32 ? launch_mfma_n<1, true>(c, qi, qo, rs, ro, a, b, dt, lsrk)
                     : launch_mfma_n<1, false>(c, qi, qo, rs, ro, a, b, dt, lsrk); break;
@@ -458,7 +480,7 @@ dg_status fill_zero(dg_ctx* c, void* p, int64_t n) {
 dg_status device_irho(dg_ctx* c, int64_t k, std::vector<double>& out) {
   const int Nq = c->re.Nq;
   out.assign(Nq, 0.0);
-  if (!plain_material(c->opt.precision, c->re.N)) {
+  if (!plain_material(c->opt.precision, c->re.N, c->mesh.K)) {
     for (int p = 0; p < Nq; ++p) {
       float v = 0.f;
       const size_t idx = dgh::mfma_material_index(c->re.N, k, p, 0);
@@ -1077,12 +1099,6 @@ hipError_t batch_stage(int N, bool f32, bool tiles, const dgb::BatchSlot* table,
   }
 }
 
-// whether a context's stage runs on element tiles or on one element per
-// workgroup, alone and in a batch
-bool batch_tiled(const dg_ctx* c) {
-  return c->re.N <= 4 || row_tiles(c->opt.precision, c->re.N, c->mesh.K);
-}
-
 // the slot of context c (state buffers in the order of its current parity)
 dgb::BatchSlot batch_slot_of(const dg_ctx* c, double dt, int64_t first) {
   dgb::BatchSlot S;
@@ -1091,7 +1107,7 @@ dgb::BatchSlot batch_slot_of(const dg_ctx* c, double dt, int64_t first) {
   float* q0 = static_cast<float*>(c->q[c->cur].p);
   float* q1 = static_cast<float*>(c->q[1 - c->cur].p);
   float* res = static_cast<float*>(c->res.p);
-  if (c->re.N <= 4) {
+  if (c->re.N <= 4 && !one_element(c)) {
     dgb::BxArgs& A = S.k.bx;
     A.q_in = q0;
     A.q_out = q1;
@@ -1113,13 +1129,13 @@ dgb::BatchSlot batch_slot_of(const dg_ctx* c, double dt, int64_t first) {
     S.nwg = (c->mesh.K + dgb::kTile - 1) / dgb::kTile;
   } else {
     dgb::BeArgs& A = S.k.be;
-    A = be_args(c);
+    A = be_args<float>(c);
     A.q_in = q0;
     A.q_out = q1;
     A.res = res;
     A.dt = float(dt);
     A.lsrk = 1;
-    S.nwg = batch_tiled(c) ? (c->mesh.K + dgb::kTile - 1) / dgb::kTile : c->mesh.K;
+    S.nwg = one_element(c) ? c->mesh.K : (c->mesh.K + dgb::kTile - 1) / dgb::kTile;
   }
   S.first = first;
   S.q[0] = q0;
@@ -1179,7 +1195,7 @@ dg_status batch_advance_impl(void* table, dgb::BatchSlot* slots, int max_slots, 
   int max_np3 = 0, max_rec3 = 0;
   for (int kind = 0, at = 0; kind < 2; ++kind)
     for (int i = 0; i < n; ++i) {
-      if (int(batch_tiled(cs[i])) != kind) continue;
+      if (int(!one_element(cs[i])) != kind) continue;
       dgb::BatchSlot& S = slots[at++];
       S = batch_slot_of(cs[i], dt[i], pos[kind]);
       pos[kind] += (S.nwg + 7) / 8 * 8;
@@ -1296,23 +1312,32 @@ dg_status dg_create(dg_ctx** out, const dg_options* opt) {
         dg_destroy(c);
         return DG_ENOMEM;
       }
+      // orders 1-4 hold the fragments of both kinds (tens of KB)
+      const bool both = opt->order <= 4;
       if (opt->precision == DG_FP32_BF16X3) {
         const std::vector<uint16_t> fr = dgh::mfma_fragments(re);
-        if (upload_raw(c, c->frags, fr.data(), fr.size()) != DG_OK) {
+        const std::vector<uint16_t> fe = both ? dgh::element_fragments(re) : std::vector<uint16_t>();
+        if (upload_raw(c, c->frags, fr.data(), fr.size()) != DG_OK ||
+            (both && upload_raw(c, c->efrags, fe.data(), fe.size()) != DG_OK)) {
           dg_destroy(c);
           return DG_ENOMEM;
         }
       } else if (opt->precision == DG_FP32) {
         const std::vector<float> fr = dgh::mfma_fragments_f32(re);
-        const std::vector<uint16_t> fr6 = dgh::mfma_fragments_bf16x6(re);   // may be empty
+        const std::vector<float> fe = both ? dgh::element_fragments_f32(re) : std::vector<float>();
+        const std::vector<uint16_t> fr6 =
+            both ? std::vector<uint16_t>() : dgh::mfma_fragments_bf16x6(re);   // may be empty
         if (upload_raw(c, c->frags, fr.data(), fr.size()) != DG_OK ||
+            (both && upload_raw(c, c->efrags, fe.data(), fe.size()) != DG_OK) ||
             (!fr6.empty() && upload_raw(c, c->frags6, fr6.data(), fr6.size()) != DG_OK)) {
           dg_destroy(c);
           return DG_ENOMEM;
         }
       } else {   // FP64 on the matrix cores
         const std::vector<double> fr = dgh::mfma_fragments_f64(re);
-        if (upload_raw(c, c->frags, fr.data(), fr.size()) != DG_OK) {
+        const std::vector<double> fe = both ? dgh::element_fragments_f64(re) : std::vector<double>();
+        if (upload_raw(c, c->frags, fr.data(), fr.size()) != DG_OK ||
+            (both && upload_raw(c, c->efrags, fe.data(), fe.size()) != DG_OK)) {
           dg_destroy(c);
           return DG_ENOMEM;
         }
@@ -1337,7 +1362,7 @@ void dg_destroy(dg_ctx* c) {
     release(c, c->trace);
     for (DevBuf* b : {&c->ops, &c->opsT, &c->fmask, &c->geo, &c->fgeo, &c->etoe, &c->etop, &c->pat,
                       &c->irho, &c->lam, &c->mu, &c->zp, &c->zs, &c->q[0], &c->q[1],
-                      &c->res, &c->frags, &c->frags6, &c->matblk, &c->nbn, &c->torder, &c->src_elem, &c->src_w,
+                      &c->res, &c->frags, &c->efrags, &c->frags6, &c->matblk, &c->nbn, &c->torder, &c->src_elem, &c->src_w,
                       &c->src_par, &c->rec_elem, &c->rec_w, &c->rec_buf, &c->src_wraw,
                       &c->adj_nbface, &c->adj_invf, &c->adj_ck, &c->adj_seg, &c->adj_r,
                       &c->adj_j, &c->adj_v, &c->adj_gb, &c->adj_hb, &c->adj_grad, &c->adj_zb,
@@ -1485,7 +1510,7 @@ dg_status dg_material_upload(dg_ctx* c, const double* rho_q, const double* cp_q,
           dgh::mfma_material(c->re.N, K, a.data(), b.data(), d.data(), c->opt.precision == DG_FP64);
       if ((s = upload_real(c, c->matblk, blk.data(), blk.size())) != DG_OK) return s;
     }
-    if (plain_material(c->opt.precision, c->re.N)) {
+    if (plain_material(c->opt.precision, c->re.N, c->mesh.K)) {
       if ((s = upload_real(c, c->irho, a.data(), nq)) != DG_OK) return s;
       if ((s = upload_real(c, c->lam, b.data(), nq)) != DG_OK) return s;
       if ((s = upload_real(c, c->mu, d.data(), nq)) != DG_OK) return s;
@@ -1939,6 +1964,9 @@ dg_status dg_footprint(int32_t order, int32_t precision, int64_t K, int32_t nsrc
       b += uint64_t(dgh::mfma_f32_frag_count(order)) * 16 +
            (order == 5 || order == 6 ? uint64_t(dgh::mfma_frag_count(order)) / 2 * 3 * 64 * 16 : 0);
     else b += uint64_t(dgh::mfma_f32_frag_count(order)) * 32;   // FP64 fragments
+    if (order <= 4)   // those of one element per workgroup
+      b += precision == DG_FP32_BF16X3 ? uint64_t(dgh::element_frag_count(order, true)) * 64 * 16
+         : uint64_t(dgh::element_frag_count(order, false)) * 64 * 4 * e;
     b += k * (9 + 16) * e + k * 4 * 4 + k * 4 + 96 * Nfp * 4;          // geometry, tables
     b += 3 * 9 * k * Np * e + 2 * sizeof(double);                      // q[2], res, clock
     b += k * NF4 * 4;                                                   // neighbour nodes
@@ -1946,7 +1974,7 @@ dg_status dg_footprint(int32_t order, int32_t precision, int64_t K, int32_t nsrc
       b += ((k + 15) / 16) * 3 * uint64_t(dgh::mfma_mats(order)) * e;   // blocked material
       b += (k + 15) / 16 * 4;                                           // tile order
     }
-    if (plain_material(precision, order)) b += 3 * k * Nq * e;          // 1/rho, lam, mu
+    if (plain_material(precision, order, K)) b += 3 * k * Nq * e;          // 1/rho, lam, mu
     b += 2 * k * Np * e;                                                // impedances
     b += uint64_t(nsrc) * (8 + 3 * Np * e + 3 * 8);                     // sources
     b += uint64_t(nrec) * (8 + Np * e) + uint64_t(trace_steps) * nrec * 3 * e;   // receivers
@@ -1988,7 +2016,7 @@ dg_status dg_material_set_weights(dg_ctx* c, const double* irho_q, const double*
           dgh::mfma_material(c->re.N, K, irho_q, lam_q, mu_q, c->opt.precision == DG_FP64);
       if ((s = upload_real(c, c->matblk, blk.data(), blk.size())) != DG_OK) return s;
     }
-    if (plain_material(c->opt.precision, c->re.N)) {
+    if (plain_material(c->opt.precision, c->re.N, c->mesh.K)) {
       if ((s = upload_real(c, c->irho, irho_q, nq)) != DG_OK) return s;
       if ((s = upload_real(c, c->lam, lam_q, nq)) != DG_OK) return s;
       if ((s = upload_real(c, c->mu, mu_q, nq)) != DG_OK) return s;

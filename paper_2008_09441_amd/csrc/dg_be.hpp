@@ -1,9 +1,14 @@
-// Fused DG elastic-wave stage with BF16x3 matrix-core contractions for
-// orders 5-7 (gfx950): one element per workgroup.
+// Fused DG elastic-wave stage on the matrix cores (gfx950): one element per
+// workgroup, for contexts of few 16-element tiles at every order (their tiles
+// would leave most CUs idle) and where a tile does not fit in LDS (FP64 at
+// orders 5-7, FP32 at order 7).
 //
-// At these orders the state and fluxes of a 16-element tile no longer fit in
-// LDS, so the MFMA columns are the element's nine fields (and then its nine
-// output components) instead of sixteen elements; columns 9-15 carry zeros.
+// The MFMA columns are the element's nine fields (and then its nine output
+// components) instead of sixteen elements; columns 9-15 carry zeros.  On a
+// small mesh a stage is one chain of latencies, of which the tile's is the
+// longer one (order 3, FP64, 384 elements: 18.4 us in tiles, 11.1 us here, of
+// which about 5 are the launch and the first loads); on a large one the
+// operators' fragments, read for each element, bound it.
 // Every dense contraction runs on v_mfma_f32_16x16x32_bf16 as a BF16x3
 // split product with FP32 accumulation, exactly as in the 16-element kernel
 // (dg_bx.hpp): the reference derivatives D_r, D_s, D_t and LIFT [HW08,

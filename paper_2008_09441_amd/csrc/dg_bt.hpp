@@ -64,9 +64,13 @@ template <typename V>
 __device__ __forceinline__ V bt_ld(const void* base, unsigned off) {
   return *reinterpret_cast<const V*>(static_cast<const char*>(base) + off);
 }
-template <typename V>
-__device__ __forceinline__ void bt_st(void* base, unsigned off, const V& v) {
-  *reinterpret_cast<V*>(static_cast<char*>(base) + off) = v;
+// four floats at any 4-byte alignment (a template argument would drop the
+// alignment of the type)
+__device__ __forceinline__ f32x4 bt_ldu(const void* base, unsigned off) {
+  return *reinterpret_cast<const f32x4u*>(static_cast<const char*>(base) + off);
+}
+__device__ __forceinline__ void bt_stu(void* base, unsigned off, const f32x4& v) {
+  *reinterpret_cast<f32x4u*>(static_cast<char*>(base) + off) = v;
 }
 
 // a workgroup barrier that no instruction moves across (conversions and cleared
@@ -394,7 +398,7 @@ __device__ __forceinline__ void bt_quad(const BeArgs& A, const BtFrags& F, const
 #pragma unroll
       for (int f = 0; f < 2; ++f) {
         if constexpr (Nq % 4 == 0) {
-          m[u][f] = bt_ld<f32x4u>(wf[f], 4u * unsigned(me + min(p0, Nq - 4)));
+          m[u][f] = bt_ldu(wf[f], 4u * unsigned(me + min(p0, Nq - 4)));
         } else {
 #pragma unroll
           for (int j = 0; j < 4; ++j)
@@ -505,7 +509,7 @@ __device__ __forceinline__ void stage_bt_run(const BeArgs& A, int64_t G, int64_t
   // past NF4 are zero: the products read them).
   constexpr int QI = (9 * KN + WV - 1) / WV;
   constexpr int FK = 32 * KF, TF = kTile * FK, IF = (TF + TH - 1) / TH;
-  f32x4u qv[QI][2];
+  f32x4 qv[QI][2];
   auto load_q = [&]() {
 #pragma unroll
     for (int i = 0; i < QI; ++i) {
@@ -513,7 +517,7 @@ __device__ __forceinline__ void stage_bt_run(const BeArgs& A, int64_t G, int64_t
       const int f = task / KN, n0 = 32 * (task - f * KN) + 8 * g;
 #pragma unroll
       for (int h = 0; h < 2; ++h)
-        qv[i][h] = bt_ld<f32x4u>(qt + f * KNp, 4u * unsigned(er * Np + min(n0 + 4 * h, Np - 4)));
+        qv[i][h] = bt_ldu(qt + f * KNp, 4u * unsigned(er * Np + min(n0 + 4 * h, Np - 4)));
     }
   };
   __bf16 fx[IF][9][P];
@@ -691,7 +695,7 @@ __device__ __forceinline__ void stage_bt_run(const BeArgs& A, int64_t G, int64_t
   const int64_t t0 = e0 * Np;
   constexpr int TW = RT / QH;
   const int tb = qh * TW;
-  f32x4u rv[TW][3], qo[TW][3];
+  f32x4 rv[TW][3], qo[TW][3];
   if (A.lsrk) {
 #pragma unroll
     for (int u = 0; u < TW; ++u)
@@ -699,8 +703,8 @@ __device__ __forceinline__ void stage_bt_run(const BeArgs& A, int64_t G, int64_t
       for (int k = 0; k < 3; ++k) {
         const int64_t fb = t0 + bt_comp(O::G, grp, three ? k : min(k, 1)) * KNp;
         const unsigned at = 4u * unsigned(er * Np + min(16 * (tb + u) + 4 * g, Np - 4));
-        rv[u][k] = bt_ld<f32x4u>(A.res + fb, at);
-        qo[u][k] = bt_ld<f32x4u>(A.q_in + fb, at);
+        rv[u][k] = bt_ldu(A.res + fb, at);
+        qo[u][k] = bt_ldu(A.q_in + fb, at);
       }
   }
   f32x4 fin[TW][3];
@@ -733,13 +737,13 @@ __device__ __forceinline__ void stage_bt_run(const BeArgs& A, int64_t G, int64_t
       if ((k == 2 && !three) || n0 >= Np || e >= ne) continue;
       const int64_t fb = t0 + bt_comp(O::G, grp, k) * KNp;
       const unsigned at = 4u * unsigned(e * Np + n0);
-      const f32x4u rr = fin[u][k];
+      const f32x4 rr = fin[u][k];
       if (A.lsrk) {
-        const f32x4u rn = A.a * rv[u][k] + A.dt * rr;
-        bt_st<f32x4u>(A.res + fb, at, rn);
-        bt_st<f32x4u>(A.q_out + fb, at, qo[u][k] + A.b * rn);
+        const f32x4 rn = A.a * rv[u][k] + A.dt * rr;
+        bt_stu(A.res + fb, at, rn);
+        bt_stu(A.q_out + fb, at, qo[u][k] + A.b * rn);
       } else {
-        bt_st<f32x4u>(A.rhs_out + fb, at, rr);
+        bt_stu(A.rhs_out + fb, at, rr);
       }
     }
   }

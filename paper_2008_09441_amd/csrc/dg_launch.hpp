@@ -22,7 +22,7 @@ template <int N>
 hipError_t stage_bx_d(const dgb::BxArgsT<double>& A, unsigned grid, hipStream_t st);
 template <int N>
 hipError_t adj_tile(const dgt::TileArgs& A, unsigned grid, hipStream_t st);
-// orders 5-7: `grid` elements
+// every order: `grid` elements
 template <int N, bool F32>
 hipError_t stage_be(const dgb::BeArgs& A, unsigned grid, hipStream_t st);
 // orders 5-7 (FP32: 5 and 6): `grid` element tiles

@@ -202,6 +202,8 @@ std::vector<uint16_t> mfma_fragments(const RefElement& re) {
 
 std::vector<uint16_t> mfma_fragments_bf16x6(const RefElement& re) {
   switch (re.N) {
+    case 3: return build_frags_e<3, 3>(re);
+    case 4: return build_frags_e<4, 3>(re);
     case 5: return build_frags_e<5, 3>(re);
     case 6: return build_frags_e<6, 3>(re);
     default: return {};
@@ -235,6 +237,36 @@ std::vector<V> build_frags_ef(const RefElement& re) {
   for (int t = 0; t < O::RT; ++t)
     for (int s = 0; s < O::KQ; ++s) put(O::OFF_P + t * O::KQ + s, re.Pq, Np, Nq, t, s);
   return out;
+}
+
+std::vector<uint16_t> element_fragments(const RefElement& re) {
+  switch (re.N) {
+    case 1: return build_frags_e<1, 2>(re);
+    case 2: return build_frags_e<2, 2>(re);
+    case 3: return build_frags_e<3, 2>(re);
+    case 4: return build_frags_e<4, 2>(re);
+    default: return mfma_fragments(re);
+  }
+}
+
+std::vector<float> element_fragments_f32(const RefElement& re) {
+  switch (re.N) {
+    case 1: return build_frags_ef<1, float>(re);
+    case 2: return build_frags_ef<2, float>(re);
+    case 3: return build_frags_ef<3, float>(re);
+    case 4: return build_frags_ef<4, float>(re);
+    default: return mfma_fragments_f32(re);
+  }
+}
+
+std::vector<double> element_fragments_f64(const RefElement& re) {
+  switch (re.N) {
+    case 1: return build_frags_ef<1, double>(re);
+    case 2: return build_frags_ef<2, double>(re);
+    case 3: return build_frags_ef<3, double>(re);
+    case 4: return build_frags_ef<4, double>(re);
+    default: return mfma_fragments_f64(re);
+  }
 }
 
 std::vector<float> mfma_fragments_f32(const RefElement& re) {
@@ -362,6 +394,18 @@ std::vector<float> adj_fragments_f32(const RefElement& re) {
     case 3: return build_adj_frags<3>(re);
     case 4: return build_adj_frags<4>(re);
     default: return {};
+  }
+}
+
+int element_frag_count(int N, bool split) {
+  switch (N) {
+    case 1: return split ? dgb::EOrd<1>::NFRAG : dgb::EFOrd<1>::NFRAG;
+    case 2: return split ? dgb::EOrd<2>::NFRAG : dgb::EFOrd<2>::NFRAG;
+    case 3: return split ? dgb::EOrd<3>::NFRAG : dgb::EFOrd<3>::NFRAG;
+    case 4: return split ? dgb::EOrd<4>::NFRAG : dgb::EFOrd<4>::NFRAG;
+    case 5: return split ? dgb::EOrd<5>::NFRAG : dgb::EFOrd<5>::NFRAG;
+    case 6: return split ? dgb::EOrd<6>::NFRAG : dgb::EFOrd<6>::NFRAG;
+    default: return split ? dgb::EOrd<7>::NFRAG : dgb::EFOrd<7>::NFRAG;
   }
 }
 

@@ -23,6 +23,15 @@ std::vector<uint16_t> mfma_fragments(const RefElement& re);
 // 16-element tiles (orders 5 and 6; empty at the others)
 std::vector<uint16_t> mfma_fragments_bf16x6(const RefElement& re);
 
+// fragments of the one-element-per-workgroup stage, which small meshes run at
+// every order: BF16x3 in the layout of EOrd, FP32 and FP64 in that of EFOrd
+// (at orders 5-7 those of mfma_fragments, _f32 and _f64)
+std::vector<uint16_t> element_fragments(const RefElement& re);
+std::vector<float> element_fragments_f32(const RefElement& re);
+std::vector<double> element_fragments_f64(const RefElement& re);
+// their count at order N (of 64 lanes; split: hi and lo of EOrd, else EFOrd)
+int element_frag_count(int N, bool split);
+
 // FP32 operator fragments of the FP32 matrix-core stage: orders 1-4 in the
 // layout of FOrd ([NF4S][4] floats), orders 5-7 in that of EFOrd
 // ([NFRAG][64 lanes][4] floats)

@@ -43,8 +43,10 @@ static int emu_rhs(int N, int64_t K, const double* vxyz, const double* period,
     d[i] = rho_q[i] * cs_q[i] * cs_q[i];
   }
   for (int64_t i = 0; i < K * Np; ++i) { zp[i] = rho_n[i] * cp_n[i]; zs[i] = rho_n[i] * cs_n[i]; }
-  if (grid < 1 || grid > 6) return 3;
-  if (grid == 3 && N >= 5) {   // FP64 matrix-core kernel, orders 5-7
+  if (grid < 1 || (grid > 6 && (grid < 8 || grid > 10 || N > 4))) return 3;
+  const bool el = grid >= 8;   // one element per workgroup below order 5
+  if (el) grid -= 7;
+  if (grid == 3 && (N >= 5 || el)) {   // FP64 matrix-core kernel, one element per workgroup
     dgb::BeArgsT<double> E{};
     std::vector<double> qd(q, q + 9 * K * Np);
     E.q_in = dupT<double>(qd);
@@ -58,9 +60,12 @@ static int emu_rhs(int N, int64_t K, const double* vxyz, const double* period,
     E.fmask = dup(fmd);
     E.irho = dupT<double>(a); E.lam = dupT<double>(b); E.mu = dupT<double>(d);
     E.zp = dupT<double>(zp); E.zs = dupT<double>(zs);
-    E.frags = reinterpret_cast<const dgb::u32x4*>(dup(dgh::mfma_fragments_f64(re)));
+    E.frags = reinterpret_cast<const dgb::u32x4*>(dup(dgh::element_fragments_f64(re)));
     E.K = K; E.a = 0.0; E.b = 1.0; E.dt = 1.0; E.lsrk = lsrk; E.upwind = upwind;
     switch (N) {
+      case 2: run_grid(int(K), [=]() { dgb::stage_be_d<2>(E); }); break;
+      case 3: run_grid(int(K), [=]() { dgb::stage_be_d<3>(E); }); break;
+      case 4: run_grid(int(K), [=]() { dgb::stage_be_d<4>(E); }); break;
       case 5: run_grid(int(K), [=]() { dgb::stage_be_d<5>(E); }); break;
       case 6: run_grid(int(K), [=]() { dgb::stage_be_d<6>(E); }); break;
       default: run_grid(int(K), [=]() { dgb::stage_be_d<7>(E); }); break;
@@ -98,7 +103,7 @@ static int emu_rhs(int N, int64_t K, const double* vxyz, const double* period,
     return 0;
   }
   std::vector<uint16_t> fr = dgh::mfma_fragments(re);
-  if (N >= 5) {   // one element per workgroup (grid 2: the FP32 kernel)
+  if (N >= 5 || el) {   // one element per workgroup (grid 2: the FP32 kernel)
     dgb::BeArgs E{};
     float* qe = alloc<float>(9 * K * Np);
     std::memcpy(qe, q, sizeof(float) * 9 * K * Np);
@@ -115,10 +120,10 @@ static int emu_rhs(int N, int64_t K, const double* vxyz, const double* period,
     E.zp = dupf(zp); E.zs = dupf(zs);
     const bool fe = grid == 2;
     if (fe) {
-      const std::vector<float> ff = dgh::mfma_fragments_f32(re);
+      const std::vector<float> ff = dgh::element_fragments_f32(re);
       E.frags = reinterpret_cast<const dgb::u32x4*>(dup(ff));
     } else {
-      E.frags = reinterpret_cast<const dgb::u32x4*>(dup(fr));
+      E.frags = reinterpret_cast<const dgb::u32x4*>(dup(dgh::element_fragments(re)));
     }
     E.K = K; E.a = 0.f; E.b = 1.f; E.dt = 1.f; E.lsrk = lsrk; E.upwind = upwind;
     const int tg = int((K + dgb::kTile - 1) / dgb::kTile);
@@ -134,6 +139,12 @@ static int emu_rhs(int N, int64_t K, const double* vxyz, const double* period,
         default: run_grid(tg, [=]() { dgb::stage_bt<7, 2>(E); }, dgb::TOrd<7, 2>::TH); break;
       }
     } else switch (N) {
+      case 2: fe ? run_grid(int(K), [=]() { dgb::stage_be<2, true>(E); })
+                 : run_grid(int(K), [=]() { dgb::stage_be<2, false>(E); }); break;
+      case 3: fe ? run_grid(int(K), [=]() { dgb::stage_be<3, true>(E); })
+                 : run_grid(int(K), [=]() { dgb::stage_be<3, false>(E); }); break;
+      case 4: fe ? run_grid(int(K), [=]() { dgb::stage_be<4, true>(E); })
+                 : run_grid(int(K), [=]() { dgb::stage_be<4, false>(E); }); break;
       case 5: fe ? run_grid(int(K), [=]() { dgb::stage_be<5, true>(E); })
                  : run_grid(int(K), [=]() { dgb::stage_be<5, false>(E); }); break;
       case 6: fe ? run_grid(int(K), [=]() { dgb::stage_be<6, true>(E); })
