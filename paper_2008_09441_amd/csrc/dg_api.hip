@@ -76,8 +76,7 @@ struct dg_ctx {
   DevBuf irho, lam, mu, zp, zs;
   DevBuf q[2], res;
   DevBuf frags;             // operator fragments of the matrix-core stages
-  DevBuf efrags;            // orders 1-4: those of one element per workgroup
-  DevBuf frags6;            // FP32, orders 5 and 6: the operators in three bf16 parts
+  DevBuf efrags;            // those of one element per workgroup (FP32, and orders 1-4)
   DevBuf matblk;            // BF16x3: material blocked by 16-element tile
   DevBuf nbn;               // BF16x3: neighbour volume node of each face node
   DevBuf torder;            // BF16x3: tile processed at each launch position
@@ -119,6 +118,7 @@ struct dg_ctx {
                             // (tiled adjoint: face-node jumps [K][4 Nfp][8])
   DevBuf adj_gradz;         // upwind: double [2][K][Np]
   DevBuf adj_frag;          // FP32 orders 1-4: fragments of the tiled adjoint kernel
+  DevBuf adj_ffrag;         // and those of its FP32-product stages
   DevBuf adj_r;             // FP32 orders 1-4: R y of every stage input of a segment,
                             // [every][5][9][K][Np] (stored by the replay)
   bool adj_ov = false;      // adj_seg and adj_r hold two segments: the replay of
@@ -295,9 +295,9 @@ dgb::BeArgsT<T> be_args(const dg_ctx* c) {
   A.mu = static_cast<const T*>(c->mu.p);
   A.zp = static_cast<const T*>(c->zp.p);
   A.zs = static_cast<const T*>(c->zs.p);
-  A.frags = static_cast<const dgb::u32x4*>(
-      c->re.N <= 4 ? c->efrags.p
-      : c->opt.precision == DG_FP32 && !one_element(c) ? c->frags6.p : c->frags.p);
+  // BF16x3 and FP64 at orders 5-7: one set for both kinds
+  A.frags = static_cast<const dgb::u32x4*>(one_element(c) && c->efrags.p ? c->efrags.p
+                                                                         : c->frags.p);
   A.K = c->mesh.K;
   A.upwind = c->opt.flux == DG_FLUX_UPWIND ? 1 : 0;
   return A;
@@ -355,7 +355,8 @@ dg_status launch_stage(dg_ctx* c, const void* q_in, void* q_out, void* res, void
   return DG_OK;
 }
 
-template <int N, bool F32, bool RST = false>
+// RST, FP: the adjoint's stages on FP32 products (stage_bx_r, stage_bx_p)
+template <int N, bool F32, bool RST = false, bool FP = false>
 hipError_t launch_mfma_n(dg_ctx* c, const float* q_in, float* q_out, float* res, float* rhs_out,
                          double a, double b, double dt, int lsrk, float* r_out = nullptr,
                          float* j_out = nullptr) {
@@ -384,8 +385,11 @@ hipError_t launch_mfma_n(dg_ctx* c, const float* q_in, float* q_out, float* res,
   if (tiles > 0x7fffffff) return hipErrorInvalidValue;
   A.r_out = r_out;
   A.j_out = j_out;
+  if constexpr (RST || FP) A.frags = static_cast<const dgb::u32x4*>(c->adj_ffrag.p);
   if constexpr (RST)
     return dgl::stage_bx_r<N>(A, unsigned(tiles), c->stream);
+  else if constexpr (FP)
+    return dgl::stage_bx_p<N>(A, unsigned(tiles), c->stream);
   else
     return dgl::stage_bx<N, F32>(A, unsigned(tiles), c->stream);
 }
@@ -412,6 +416,23 @@ hipError_t launch_mfma_e(dg_ctx* c, const float* q_in, float* q_out, float* res,
   }
   // one workgroup per element
   return dgl::stage_be<N, F32>(A, unsigned(c->mesh.K), c->stream);
+}
+
+// an FP32 LSRK stage on one element per workgroup, whatever the size
+template <int N>
+hipError_t launch_element_f32(dg_ctx* c, const float* q_in, float* q_out, float* res, double a,
+                              double b, double dt) {
+  dgb::BeArgs A = be_args<float>(c);
+  A.frags = static_cast<const dgb::u32x4*>(c->efrags.p);
+  A.q_in = q_in;
+  A.q_out = q_out;
+  A.res = res;
+  A.a = float(a);
+  A.b = float(b);
+  A.dt = float(dt);
+  A.lsrk = 1;
+  if (c->mesh.K > 0x7fffffff) return hipErrorInvalidValue;
+  return dgl::stage_be<N, true>(A, unsigned(c->mesh.K), c->stream);
 }
 
 dg_status launch_mfma(dg_ctx* c, const void* q_in, void* q_out, void* res, void* rhs_out,
@@ -454,6 +475,33 @@ dg_status launch_mfma(dg_ctx* c, const void* q_in, void* q_out, void* res, void*
   }
   if (e != hipSuccess)
     return fail(c, DG_EDEVICE, std::string("matrix-core stage launch: ") + hipGetErrorString(e));
+  return DG_OK;
+}
+
+// One LSRK stage of the adjoint's forward run and of its generic replay: in FP32
+// on FP32 products whatever the size (see stage_bx_p), else the context's stage.
+// adj_tables has run.
+dg_status stage(dg_ctx* c, const void* q_in, void* q_out, void* res, void* rhs_out, double a,
+                double b, double dt, int lsrk);
+dg_status adj_stage(dg_ctx* c, const void* q_in, void* q_out, void* res, double a, double b,
+                    double dt) {
+  if (c->opt.precision != DG_FP32) return stage(c, q_in, q_out, res, nullptr, a, b, dt, 1);
+  const float* qi = static_cast<const float*>(q_in);
+  float* qo = static_cast<float*>(q_out);
+  float* rs = static_cast<float*>(res);
+  hipError_t e;
+  switch (c->re.N) {
+    case 1: e = launch_mfma_n<1, true, false, true>(c, qi, qo, rs, nullptr, a, b, dt, 1); break;
+    case 2: e = launch_mfma_n<2, true, false, true>(c, qi, qo, rs, nullptr, a, b, dt, 1); break;
+    case 3: e = launch_mfma_n<3, true, false, true>(c, qi, qo, rs, nullptr, a, b, dt, 1); break;
+    case 4: e = launch_mfma_n<4, true, false, true>(c, qi, qo, rs, nullptr, a, b, dt, 1); break;
+    case 5: e = launch_element_f32<5>(c, qi, qo, rs, a, b, dt); break;
+    case 6: e = launch_element_f32<6>(c, qi, qo, rs, a, b, dt); break;
+    case 7: e = launch_element_f32<7>(c, qi, qo, rs, a, b, dt); break;
+    default: e = hipErrorInvalidValue;
+  }
+  if (e != hipSuccess)
+    return fail(c, DG_EDEVICE, std::string("adjoint stage launch: ") + hipGetErrorString(e));
   return DG_OK;
 }
 
@@ -715,6 +763,8 @@ dg_status adj_tables(dg_ctx* c) {
   if (adj_tiled(c)) {
     const std::vector<float> fr = dgh::adj_fragments_f32(re);
     if ((st = upload_raw(c, c->adj_frag, fr.data(), fr.size())) != DG_OK) return st;
+    const std::vector<float> ff = dgh::mfma_fragments_f32(re);
+    if ((st = upload_raw(c, c->adj_ffrag, ff.data(), ff.size())) != DG_OK) return st;
   }
   if ((st = upload_raw(c, c->adj_nbface, nbf.data(), nbf.size())) != DG_OK) return st;
   return upload_raw(c, c->adj_invf, invf.data(), invf.size());
@@ -1002,8 +1052,7 @@ dg_status adj_backward_t(dg_ctx* c, const T* resid) {
       if ((s = fill_zero(c, res, n)) != DG_OK) return s;
       for (int q = 0; q < 5 && (q < 4 || i + 1 < n1); ++q) {
         T* out = q < 4 ? y + (q + 1) * n : y + 5 * n;   // stage 5: the next step's y_0
-        if ((s = stage(c, y + q * n, out, res, nullptr, kRkA[q], kRkB[q], dt, 1)) != DG_OK)
-          return s;
+        if ((s = adj_stage(c, y + q * n, out, res, kRkA[q], kRkB[q], dt)) != DG_OK) return s;
         if ((s = launch_sources(c, res, out, ti + kRkC[q] * dt, dt, kRkB[q] * dt)) != DG_OK)
           return s;
       }
@@ -1323,13 +1372,15 @@ dg_status dg_create(dg_ctx** out, const dg_options* opt) {
           return DG_ENOMEM;
         }
       } else if (opt->precision == DG_FP32) {
-        const std::vector<float> fr = dgh::mfma_fragments_f32(re);
-        const std::vector<float> fe = both ? dgh::element_fragments_f32(re) : std::vector<float>();
-        const std::vector<uint16_t> fr6 =
-            both ? std::vector<uint16_t>() : dgh::mfma_fragments_bf16x6(re);   // may be empty
-        if (upload_raw(c, c->frags, fr.data(), fr.size()) != DG_OK ||
-            (both && upload_raw(c, c->efrags, fe.data(), fe.size()) != DG_OK) ||
-            (!fr6.empty() && upload_raw(c, c->frags6, fr6.data(), fr6.size()) != DG_OK)) {
+        // tiles take FP32 fragments (orders 1, 2) or three bf16 parts (3-6), one
+        // element per workgroup FP32 fragments
+        const std::vector<float> fe = dgh::element_fragments_f32(re);
+        const std::vector<float> ff =
+            opt->order <= 2 ? dgh::mfma_fragments_f32(re) : std::vector<float>();
+        const std::vector<uint16_t> f6 = dgh::mfma_fragments_bf16x6(re);
+        if ((!ff.empty() && upload_raw(c, c->frags, ff.data(), ff.size()) != DG_OK) ||
+            upload_raw(c, c->efrags, fe.data(), fe.size()) != DG_OK ||
+            (!f6.empty() && upload_raw(c, c->frags, f6.data(), f6.size()) != DG_OK)) {
           dg_destroy(c);
           return DG_ENOMEM;
         }
@@ -1362,11 +1413,11 @@ void dg_destroy(dg_ctx* c) {
     release(c, c->trace);
     for (DevBuf* b : {&c->ops, &c->opsT, &c->fmask, &c->geo, &c->fgeo, &c->etoe, &c->etop, &c->pat,
                       &c->irho, &c->lam, &c->mu, &c->zp, &c->zs, &c->q[0], &c->q[1],
-                      &c->res, &c->frags, &c->efrags, &c->frags6, &c->matblk, &c->nbn, &c->torder, &c->src_elem, &c->src_w,
+                      &c->res, &c->frags, &c->efrags, &c->matblk, &c->nbn, &c->torder, &c->src_elem, &c->src_w,
                       &c->src_par, &c->rec_elem, &c->rec_w, &c->rec_buf, &c->src_wraw,
                       &c->adj_nbface, &c->adj_invf, &c->adj_ck, &c->adj_seg, &c->adj_r,
                       &c->adj_j, &c->adj_v, &c->adj_gb, &c->adj_hb, &c->adj_grad, &c->adj_zb,
-                      &c->adj_gradz, &c->adj_frag, &c->adj_trace})
+                      &c->adj_gradz, &c->adj_frag, &c->adj_ffrag, &c->adj_trace})
       release(c, *b);
   }
   delete c;
@@ -1412,7 +1463,7 @@ dg_status dg_mesh_upload(dg_ctx* c, int64_t K, const double* vxyz, const double*
     for (DevBuf* b : {&c->src_elem, &c->src_w, &c->src_par, &c->rec_elem, &c->rec_w, &c->rec_buf,
                       &c->trace, &c->src_wraw, &c->adj_nbface, &c->adj_invf, &c->adj_ck,
                       &c->adj_seg, &c->adj_r, &c->adj_j, &c->adj_v, &c->adj_gb, &c->adj_hb,
-                      &c->adj_grad, &c->adj_zb, &c->adj_gradz, &c->adj_frag, &c->adj_trace})
+                      &c->adj_grad, &c->adj_zb, &c->adj_gradz, &c->adj_frag, &c->adj_ffrag, &c->adj_trace})
       release(c, *b);
     c->adj_ready = false;
     c->adj_ov_failed = c->adj_j_failed = 0;
@@ -1960,11 +2011,11 @@ dg_status dg_footprint(int32_t order, int32_t precision, int64_t K, int32_t nsrc
     b += (3 * Np * NpP + NF4 * NpP + Np * QP + QP * NpP) * e;           // transposed operators
     b += NF4 * 4;                                                       // face masks
     if (precision == DG_FP32_BF16X3) b += uint64_t(dgh::mfma_frag_count(order)) * 64 * 8 * 2;
-    else if (precision == DG_FP32)
-      b += uint64_t(dgh::mfma_f32_frag_count(order)) * 16 +
-           (order == 5 || order == 6 ? uint64_t(dgh::mfma_frag_count(order)) / 2 * 3 * 64 * 16 : 0);
-    else b += uint64_t(dgh::mfma_f32_frag_count(order)) * 32;   // FP64 fragments
-    if (order <= 4)   // those of one element per workgroup
+    else if (precision == DG_FP64) b += uint64_t(dgh::mfma_f64_frag_count(order)) * 32;
+    else   // FP32: FP32 fragments (orders 1, 2) or three parts
+      b += order <= 2 ? uint64_t(dgh::mfma_f64_frag_count(order)) * 16
+                      : uint64_t(dgh::mfma_frag_count(order)) / 2 * 3 * 64 * 16;
+    if (order <= 4 || precision == DG_FP32)   // those of one element per workgroup
       b += precision == DG_FP32_BF16X3 ? uint64_t(dgh::element_frag_count(order, true)) * 64 * 16
          : uint64_t(dgh::element_frag_count(order, false)) * 64 * 4 * e;
     b += k * (9 + 16) * e + k * 4 * 4 + k * 4 + 96 * Nfp * 4;          // geometry, tables
@@ -2111,7 +2162,15 @@ dg_status dg_adjoint_forward(dg_ctx* c, double t0, double dt, int64_t nsteps, in
       if (i % every == 0)
         DG_HIP(c, hipMemcpyAsync(ck + S * size_t(i / every), c->q[c->cur].p, S,
                                  hipMemcpyDeviceToDevice, c->stream));
-      if ((s = dg_step(c, t0 + double(i) * dt, dt)) != DG_OK) return s;
+      const double ti = t0 + double(i) * dt;
+      if (!std::isfinite(ti)) return fail(c, DG_EINVAL, "step: non-finite t/dt");
+      for (int st = 0; st < 5; ++st) {
+        void *qi = c->q[c->cur].p, *qo = c->q[1 - c->cur].p;
+        if ((s = adj_stage(c, qi, qo, c->res.p, kRkA[st], kRkB[st], dt)) != DG_OK) return s;
+        if ((s = launch_sources(c, c->res.p, qo, ti + kRkC[st] * dt, dt, kRkB[st] * dt)) != DG_OK)
+          return s;
+        c->cur = 1 - c->cur;
+      }
       if ((s = launch_receivers(c, tr + per * size_t(i))) != DG_OK) return s;
     }
     DG_HIP(c, copy_sync(c, trace, tr, tb, hipMemcpyDeviceToHost));

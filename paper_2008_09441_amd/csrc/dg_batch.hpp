@@ -62,7 +62,7 @@ __device__ __forceinline__ int batch_slot(const BatchSlot* slots, int nslots, in
 }
 
 template <int N, bool F32>
-__global__ __launch_bounds__(kThreads, 2) void stage_bx_batch(const BatchSlot* slots, int nslots,
+__global__ __launch_bounds__(kThreads, bx_waves(N)) void stage_bx_batch(const BatchSlot* slots, int nslots,
                                                               int par, float a, float b) {
   const int64_t bid = blockIdx.x;
   const int s = batch_slot(slots, nslots, bid);

@@ -87,6 +87,21 @@ struct BeLds {
   static constexpr int BYTES = USED > FLOOR ? USED : FLOOR;
 };
 
+// the BF16x3 product and split, parts as separate values
+__device__ __forceinline__ f32x4 mma3(const u32x4& ah, const u32x4& al, const bf16x8& bh,
+                                      const bf16x8& bl, f32x4 c) {
+  c = mma(ah, bh, c);
+  c = mma(ah, bl, c);
+  c = mma(al, bh, c);
+  return c;
+}
+__device__ __forceinline__ void split8(const float* v, bf16x8& hi, bf16x8& lo) {
+  bf16x8 o[2];
+  split8<2>(v, o);
+  hi = o[0];
+  lo = o[1];
+}
+
 // Operator fragments in flight per wave: each BF16x3 product waits for its
 // two fragments (an L2 round trip), so they are loaded this many products
 // ahead

@@ -81,17 +81,6 @@ __device__ __forceinline__ void bt_sync() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
-// Uses accumulators where they are complete: products have no side effect, and
-// the compiler sinks those whose result is read in a later block into it, with
-// all their operands kept in registers until then.
-template <int M>
-__device__ __forceinline__ void bt_done(f32x4 (&v)[M]) {
-#if defined(__HIP_DEVICE_COMPILE__)
-#pragma unroll
-  for (int i = 0; i < M; ++i) asm volatile("" : "+v"(v[i]));
-#endif
-}
-
 template <int N, int P>
 struct TOrd {
   static constexpr int Np = (N + 1) * (N + 2) * (N + 3) / 6;
@@ -165,45 +154,10 @@ __device__ __forceinline__ void bt_split(const float* v, int n, __bf16 (&o)[P]) 
 }
 
 template <int P>
-__device__ __forceinline__ void bt_split8(const float* v, bf16x8 (&o)[P]) {
-  float r[8];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) r[j] = v[j];
+__device__ __forceinline__ void bt_frag(const FragBuf& F, int f, u32x4 (&a)[P]) {
 #pragma unroll
   for (int p = 0; p < P; ++p)
-#pragma unroll
-    for (int j = 0; j < 8; j += 2) {
-      const bf16x2 h = __builtin_convertvector(f32x2{r[j], r[j + 1]}, bf16x2);
-      const f32x2 d = f32x2{r[j], r[j + 1]} - __builtin_convertvector(h, f32x2);
-      o[p][j] = h[0];
-      o[p][j + 1] = h[1];
-      r[j] = d[0];
-      r[j + 1] = d[1];
-    }
-}
-
-// the part products of a split product, A part and B part: P = 2 in the order
-// of the other BF16x3 kernels, P = 3 from the smallest up
-template <int P>
-constexpr int kBtProd = P == 2 ? 3 : 6;
-__host__ __device__ constexpr int bt_pa(int P, int k) {
-  return P == 2 ? (k == 2 ? 1 : 0) : (k == 0 ? 2 : k == 2 || k == 3 ? 1 : 0);
-}
-__host__ __device__ constexpr int bt_pb(int P, int k) {
-  return P == 2 ? (k == 1 ? 1 : 0) : (k == 1 ? 2 : k == 2 || k == 4 ? 1 : 0);
-}
-
-// operator fragments: a buffer descriptor, a uniform fragment offset and the
-// lane's 16-byte slot (one register of address for every fragment load)
-struct BtFrags {
-  __amdgpu_buffer_rsrc_t r;
-  int lane16;
-};
-template <int P>
-__device__ __forceinline__ void bt_frag(const BtFrags& F, int f, u32x4 (&a)[P]) {
-#pragma unroll
-  for (int p = 0; p < P; ++p)
-    a[p] = __builtin_amdgcn_raw_buffer_load_b128(F.r, F.lane16, (f * P + p) * 1024, 0);
+    a[p] = F.load(f * P + p);
 }
 
 // B operand of component c, K step s (of KS) from a buffer; l0 = 16 g + (e ^ g)
@@ -254,7 +208,7 @@ __device__ __forceinline__ void bt_put4(bf16x8* buf, int KS, int c, int t, int g
 // LIFT f and the derivatives at one node tile t for the components of group h:
 // r[i] += rows 4 g + j of component C0 + i
 template <int N, int P, int H>
-__device__ __forceinline__ void bt_lift(const BtFrags& F, const bf16x8* sf, int t, int l0,
+__device__ __forceinline__ void bt_lift(const FragBuf& F, const bf16x8* sf, int t, int l0,
                                         f32x4 (&r)[9]) {
   using O = TOrd<N, P>;
   constexpr BtRole R = bt_role(O::DH, H);
@@ -274,11 +228,11 @@ __device__ __forceinline__ void bt_lift(const BtFrags& F, const bf16x8* sf, int 
         if (j % NG == 0 && s + 1 < O::KF)
           bt_frag<P>(F, O::OFF_L + t * O::KF + s + 1, fa[(s + 1) & 1]);
 #pragma unroll
-        for (int x = 0; x < kBtProd<P>; ++x)
+        for (int x = 0; x < kProd<P>; ++x)
 #pragma unroll
           for (int k = 0; k < GS; ++k) {
             const int c = j % NG * GS + k;
-            r[c] = mma(fa[s & 1][bt_pa(P, x)], b[k][bt_pb(P, x)], r[c]);
+            r[c] = mma(fa[s & 1][prod_a(P, x)], b[k][prod_b(P, x)], r[c]);
           }
       });
 }
@@ -286,7 +240,7 @@ __device__ __forceinline__ void bt_lift(const BtFrags& F, const bf16x8* sf, int 
 // D_r q, D_s q, D_t q of the group's fields, then the chain rule
 // r_c += sum_d sum_j G_dj w(c, j) D_d q_{f(c,j)}
 template <int N, int P, int H>
-__device__ __forceinline__ void bt_deriv(const BtFrags& F, const bf16x8* sn, int t, int l0,
+__device__ __forceinline__ void bt_deriv(const FragBuf& F, const bf16x8* sn, int t, int l0,
                                          const float (&Ge)[9], f32x4 (&r)[9]) {
   using O = TOrd<N, P>;
   constexpr BtRole R = bt_role(O::DH, H);
@@ -304,7 +258,7 @@ __device__ __forceinline__ void bt_deriv(const BtFrags& F, const bf16x8* sn, int
   // with three parts, the five small products of every K step come before the
   // leading product of any: the accumulators then round at full size KN times,
   // not 6 KN times (a derivative's sum cancels, so its roundings weigh most)
-  constexpr int NY = P == 3 ? kBtProd<P> - 1 : kBtProd<P>;
+  constexpr int NY = P == 3 ? kProd<P> - 1 : kProd<P>;
   bt_pipe<KN * R.nf, 1, P>(
       [&](int j, bf16x8(&b)[1][P]) { bt_bread<P>(sn, KN, R.f0 + j % R.nf, j / R.nf, l0, b[0]); },
       [&](int j, const bf16x8(&b)[1][P]) {
@@ -319,7 +273,7 @@ __device__ __forceinline__ void bt_deriv(const BtFrags& F, const bf16x8* sn, int
         for (int y = 0; y < NY; ++y)
 #pragma unroll
           for (int x = 0; x < 3; ++x)
-            d[x][f] = mma(fa[s % NB][x][bt_pa(P, y)], b[0][bt_pb(P, y)], d[x][f]);
+            d[x][f] = mma(fa[s % NB][x][prod_a(P, y)], b[0][prod_b(P, y)], d[x][f]);
         if (NB == 1 && f == R.nf - 1 && s + 1 < KN) next();
       });
   if constexpr (P == 3) {
@@ -328,8 +282,7 @@ __device__ __forceinline__ void bt_deriv(const BtFrags& F, const bf16x8* sn, int
     for (int s = 0; s < KN; ++s)
 #pragma unroll
       for (int x = 0; x < 3; ++x)
-        fh[s][x] = __builtin_amdgcn_raw_buffer_load_b128(
-            F.r, F.lane16, (O::OFF_D + (x * RT + t) * KN + s) * P * 1024, 0);
+        fh[s][x] = F.load((O::OFF_D + (x * RT + t) * KN + s) * P);
     bt_pipe<KN * R.nf, 1, 1>(
         [&](int j, bf16x8(&b)[1][1]) {
           b[0][0] = sn[((R.f0 + j % R.nf) * KN + j / R.nf) * P * 64 + (l0 ^ (4 * (j / R.nf & 3)))];
@@ -378,7 +331,7 @@ __device__ __forceinline__ void bt_rput(bf16x8* sn, int t, int g, int e, const f
 // another.  A K step is 2 KN items of V_q and RT items of P_q, one operator
 // fragment each, fetched PD items ahead.
 template <int N, int P, int NC>
-__device__ __forceinline__ void bt_quad(const BeArgs& A, const BtFrags& F, const bf16x8* sn,
+__device__ __forceinline__ void bt_quad(const BeArgs& A, const FragBuf& F, const bf16x8* sn,
                                         int64_t e0, int er, int g, int l0, int grp, int kb, int ke,
                                         f32x4 (&out)[TOrd<N, P>::RT][3]) {
   using O = TOrd<N, P>;
@@ -433,10 +386,10 @@ __device__ __forceinline__ void bt_quad(const BeArgs& A, const BtFrags& F, const
     for (int j = 0; j < NV; ++j) {
       if (j + 1 < NV) bread((j + 1) % KN, b[(j + 1) & 1]);
 #pragma unroll
-      for (int x = 0; x < kBtProd<P>; ++x)
+      for (int x = 0; x < kProd<P>; ++x)
 #pragma unroll
         for (int k = 0; k < NC; ++k)
-          w[j / KN][k] = mma(fr[j % PD][bt_pa(P, x)], b[j & 1][k][bt_pb(P, x)], w[j / KN][k]);
+          w[j / KN][k] = mma(fr[j % PD][prod_a(P, x)], b[j & 1][k][prod_b(P, x)], w[j / KN][k]);
       fetch(c, j + PD);
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -459,17 +412,17 @@ __device__ __forceinline__ void bt_quad(const BeArgs& A, const BtFrags& F, const
       float v[8];
 #pragma unroll
       for (int j = 0; j < 8; ++j) v[j] = w[j / 4][k][j % 4];
-      bt_split8<P>(v, q[k]);
+      split8<P>(v, q[k]);
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int t = 0; t < RT; ++t) {
       const int j = NV + t;
 #pragma unroll
-      for (int x = 0; x < kBtProd<P>; ++x)
+      for (int x = 0; x < kProd<P>; ++x)
 #pragma unroll
         for (int k = 0; k < NC; ++k)
-          out[t][k] = mma(fr[j % PD][bt_pa(P, x)], q[k][bt_pb(P, x)], out[t][k]);
+          out[t][k] = mma(fr[j % PD][prod_a(P, x)], q[k][prod_b(P, x)], out[t][k]);
       fetch(c, j + PD);
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -642,16 +595,14 @@ __device__ __forceinline__ void stage_bt_run(const BeArgs& A, int64_t G, int64_t
   for (int i = 0; i < 9; ++i) Ge[i] = bt_ld<float>(A.geo + e0 * 9, 4u * unsigned(er * 9 + i));
   bt_sync();
 
-  const BtFrags F = {__builtin_amdgcn_make_buffer_rsrc(const_cast<u32x4*>(A.frags), 0,
-                                                       O::NFRAG * 1024, 0x00020000),
-                     lane * 16};
+  const FragBuf F(A.frags, O::NFRAG, lane);
 
   // 2: r = LIFT f
   const int dt = wave % RT, dh = wave / RT;
   f32x4 r[9] = {};
   if (O::DH == 1 || dh == 0) bt_lift<N, P, 0>(F, sf, dt, l0, r);
   else bt_lift<N, P, O::DH - 1>(F, sf, dt, l0, r);
-  bt_done(r);
+  mma_done(r);
   bt_sync();
 
   // 3: the state into LDS, rows past Np zero
@@ -664,7 +615,7 @@ __device__ __forceinline__ void stage_bt_run(const BeArgs& A, int64_t G, int64_t
 #pragma unroll
       for (int j = 0; j < 8; ++j) v[j] = n0 + 4 * (j / 4) < Np ? qv[i][j / 4][j % 4] : 0.f;
       bf16x8 o[P];
-      bt_split8<P>(v, o);
+      split8<P>(v, o);
 #pragma unroll
       for (int p = 0; p < P; ++p) sn[((f * KN + s) * P + p) * 64 + (l0 ^ (4 * (s & 3)))] = o[p];
     }
@@ -674,7 +625,7 @@ __device__ __forceinline__ void stage_bt_run(const BeArgs& A, int64_t G, int64_t
   // 4: derivatives; 5: r into LDS
   if (O::DH == 1 || dh == 0) bt_deriv<N, P, 0>(F, sn, dt, l0, Ge, r);
   else bt_deriv<N, P, O::DH - 1>(F, sn, dt, l0, Ge, r);
-  bt_done(r);
+  mma_done(r);
   bt_sync();
   if (O::DH == 1 || dh == 0) bt_rput<N, P, 0>(sn, dt, g, e, r);
   else bt_rput<N, P, O::DH - 1>(sn, dt, g, e, r);

@@ -40,6 +40,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "dg_bx_layout.hpp"
 
@@ -122,29 +123,100 @@ __device__ __forceinline__ f32x4 mma(const u32x4& a, const bf16x8& b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), b, c, 0, 0, 0);
 }
 
-__device__ __forceinline__ f32x4 mma3(const u32x4& ah, const u32x4& al, const bf16x8& bh,
-                                      const bf16x8& bl, f32x4 c) {
-  c = mma(ah, bh, c);
-  c = mma(ah, bl, c);
-  c = mma(al, bh, c);
-  return c;
-}
-
-// hi = bf16(x) (round to nearest even), lo = bf16(x - hi), converted in
-// pairs (one packed conversion per pair and part)
-__device__ __forceinline__ void split8(const float* v, bf16x8& hi, bf16x8& lo) {
+// x as P bf16 parts, each the rounding (to nearest even) of what the parts before
+// leave, converted in pairs (one packed conversion per pair and part): two parts
+// hold 16 bits, three all 24 of an FP32 value
+template <int P>
+__device__ __forceinline__ void split8(const float* v, bf16x8 (&o)[P]) {
 #pragma unroll
-  for (int p = 0; p < 4; ++p) {
-    const f32x2 x = {v[2 * p], v[2 * p + 1]};
-    const bf16x2 h = __builtin_convertvector(x, bf16x2);
-    const f32x2 r = x - __builtin_convertvector(h, f32x2);
-    const bf16x2 l = __builtin_convertvector(r, bf16x2);
-    hi[2 * p] = h[0];
-    hi[2 * p + 1] = h[1];
-    lo[2 * p] = l[0];
-    lo[2 * p + 1] = l[1];
+  for (int k = 0; k < 4; ++k) {
+    f32x2 r = {v[2 * k], v[2 * k + 1]};
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+      const bf16x2 h = __builtin_convertvector(r, bf16x2);
+      if (p + 1 < P) r = r - __builtin_convertvector(h, f32x2);
+      o[p][2 * k] = h[0];
+      o[p][2 * k + 1] = h[1];
+    }
   }
 }
+
+// The part products of a split product A B: A part prod_a and B part prod_b of
+// product k < kProd<P>.  P = 2 (BF16x3): hi hi, hi lo, lo hi.  P = 3 (FP32): the
+// six whose order is not below 2^-24, from the smallest up.
+template <int P>
+constexpr int kProd = P == 2 ? 3 : 6;
+__host__ __device__ constexpr int prod_a(int P, int k) {
+  return P == 2 ? (k == 2 ? 1 : 0) : (k == 0 ? 2 : k == 2 || k == 3 ? 1 : 0);
+}
+__host__ __device__ constexpr int prod_b(int P, int k) {
+  return P == 2 ? (k == 1 ? 1 : 0) : (k == 1 ? 2 : k == 2 || k == 4 ? 1 : 0);
+}
+template <int P, bool APART = P == 3>
+__device__ __forceinline__ f32x4 mma_split(const u32x4 (&a)[P], const bf16x8 (&b)[P], f32x4 c) {
+  if constexpr (!APART) {
+#pragma unroll
+    for (int k = 0; k < kProd<P>; ++k) c = mma(a[prod_a(P, k)], b[prod_b(P, k)], c);
+    return c;
+  } else {
+    // the small products on their own, so that c rounds at full size twice a step
+    // and not six times (an FP32 right-hand side of order 4 is 2.0e-6 off its
+    // FP64 value with six, less than the 1.7e-6 of FP32 products with two)
+    f32x4 d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k + 1 < kProd<P>; ++k) d = mma(a[prod_a(P, k)], b[prod_b(P, k)], d);
+    return mma(a[0], b[0], c) + d;
+  }
+}
+
+// Uses accumulators where they are complete: products have no side effect, and
+// the compiler sinks those whose result is read in a later block into it, with
+// all their operands kept in registers until then.
+template <int M>
+__device__ __forceinline__ void mma_done(f32x4 (&v)[M]) {
+#if defined(__HIP_DEVICE_COMPILE__)
+#pragma unroll
+  for (int i = 0; i < M; ++i) asm volatile("" : "+v"(v[i]));
+#endif
+}
+
+// operator fragments (64 lanes x 16 bytes each): a buffer descriptor, a uniform
+// fragment offset and the lane's slot, so that one register addresses them all
+// (BF16x3, order 4: 233 registers and 1685 us at 663,552 elements, against 247
+// and 1714 with a 64-bit address per fragment row)
+struct FragBuf {
+  __amdgpu_buffer_rsrc_t r;
+  int lane16;
+  __device__ FragBuf(const void* frags, int count, int lane)
+      : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(frags), 0, count * 1024, 0x00020000)),
+        lane16(lane * 16) {}
+  __device__ __forceinline__ u32x4 load(int f) const {
+    return __builtin_amdgcn_raw_buffer_load_b128(r, lane16, f * 1024, 0);
+  }
+};
+
+// the same for the four-value fragments of FOrd (64 lanes x 4 values each).  With
+// 64-bit addresses the FP64 stage takes 876 us at order 4 and 384 at order 3
+// (82,944 elements), with these 848 and 377; FP32 at orders 1 and 2 is unchanged.
+template <typename T>
+struct FragBufF {
+  __amdgpu_buffer_rsrc_t r;
+  int off;
+  __device__ FragBufF(const void* frags, int count, int lane)
+      : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(frags), 0, count * int(4 * sizeof(T)),
+                                            0x00020000)),
+        off(lane * int(4 * sizeof(T))) {}
+  __device__ __forceinline__ v4_t<T> load(int f) const {
+    union {
+      u32x4 u[sizeof(T) / 4];
+      v4_t<T> v;
+    } x;
+#pragma unroll
+    for (int i = 0; i < int(sizeof(T)) / 4; ++i)
+      x.u[i] = __builtin_amdgcn_raw_buffer_load_b128(r, off + 16 * i, f * int(256 * sizeof(T)), 0);
+    return x.v;
+  }
+};
 
 // LDS use of one workgroup, in values of T, and its padded allocation in bytes
 template <int N, typename T = float>
@@ -161,6 +233,9 @@ struct BLds {
   static constexpr int SRL = sizeof(T) == 4 ? 3 * O::SVQ * 2 * 64 * 4 : 0;
   static constexpr int SU = SF > RO + SRL ? SF : RO + SRL;
   static constexpr int OFF_U = (SQ + SG + SZ + 3) & ~3;  // 16-byte aligned union
+  // FP32: the third part of those operands, over the impedances (phase B's)
+  static constexpr int OFF_P3 = (SQ + SG + 3) & ~3;
+  static constexpr bool PARK3 = OFF_P3 + 3 * O::SVQ * 64 * 4 <= OFF_U;
   static constexpr int USED = (OFF_U + SU) * int(sizeof(T));
   // Padded so that the workgroups one CU can hold (160 KiB of LDS) never use
   // more than 128 KiB together (at most 3 per CU at >40 KiB each, 2 at
@@ -171,8 +246,8 @@ struct BLds {
 };
 
 // Phase C for wave W: acc[i][t] = rows 16 t + 4 g + j of r_{comp i}
-template <int N, int W>
-__device__ __forceinline__ void vol_lift(const BxArgs& A, const float* sq, const float* sg,
+template <int N, int W, int P>
+__device__ __forceinline__ void vol_lift(const BxArgs& A, const FragBuf& F, const float* sq, const float* sg,
                                          const float* sF, int lane, f32x4 (&acc)[3][BOrd<N>::RT]) {
   using O = BOrd<N>;
   constexpr int Np = O::Np, NF4 = O::NF4, RT = O::RT, SN = O::SN, SVL = O::SVL;
@@ -188,19 +263,19 @@ __device__ __forceinline__ void vol_lift(const BxArgs& A, const float* sq, const
 
   // operator fragments are prefetched one K step ahead (the fragment reads
   // hit L2; without the prefetch each step waits for its own)
-  u32x4 fc[RT][2], fn[RT][2];
+  u32x4 fc[RT][P], fn[RT][P];
 #pragma unroll
   for (int t = 0; t < RT; ++t)
 #pragma unroll
-    for (int h = 0; h < 2; ++h) fc[t][h] = A.frags[(O::OFF_V + t * SVL * 2 + h) * 64 + lane];
+    for (int h = 0; h < P; ++h) fc[t][h] = F.load((O::OFF_V + t * SVL) * P + h);
 #pragma unroll
   for (int s = 0; s < SVL; ++s) {
     if (s + 1 < SVL) {
 #pragma unroll
       for (int t = 0; t < RT; ++t)
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
-          fn[t][h] = A.frags[(O::OFF_V + (t * SVL + s + 1) * 2 + h) * 64 + lane];
+        for (int h = 0; h < P; ++h)
+          fn[t][h] = F.load((O::OFF_V + t * SVL + s + 1) * P + h);
     }
     __builtin_amdgcn_sched_barrier(0);
     float bv[NC][8];
@@ -243,15 +318,23 @@ __device__ __forceinline__ void vol_lift(const BxArgs& A, const float* sq, const
         for (int i = 0; i < NC; ++i) bv[i][j] = sF[(wave_comp(W, i) * NF4 + jf) * kES + e];
       }
     }
-    bf16x8 bh[NC], bl[NC];
+    bf16x8 b[NC][P];
 #pragma unroll
-    for (int i = 0; i < NC; ++i) split8(bv[i], bh[i], bl[i]);
+    for (int i = 0; i < NC; ++i) split8<P>(bv[i], b[i]);
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+#pragma unroll
+      for (int i = 0; i < NC; ++i) acc[i][t] = mma_split<P>(fc[t], b[i], acc[i][t]);
+      if (P == 3) __builtin_amdgcn_sched_barrier(0);   // registers
+    }
 #pragma unroll
     for (int t = 0; t < RT; ++t)
 #pragma unroll
-      for (int i = 0; i < NC; ++i) acc[i][t] = mma3(fc[t][0], fc[t][1], bh[i], bl[i], acc[i][t]);
+      for (int h = 0; h < P; ++h) fc[t][h] = fn[t][h];
+  }
+  if constexpr (P == 3) {
 #pragma unroll
-    for (int t = 0; t < RT; ++t) fc[t][0] = fn[t][0], fc[t][1] = fn[t][1];
+    for (int i = 0; i < NC; ++i) mma_done(acc[i]);
   }
 }
 
@@ -273,10 +356,11 @@ __device__ __forceinline__ void mat_chunk(const BxArgsT<T>& A, int64_t tile, int
 
 // Phase D for wave W: V_q, material, P_q; the nodal result goes to sr.  m0
 // holds the material of chunk 0 (loaded before phase C).
-template <int N, int W>
-__device__ __forceinline__ void quad_proj(const BxArgs& A, int64_t tile, int lane,
+template <int N, int W, int P>
+__device__ __forceinline__ void quad_proj(const BxArgs& A, const FragBuf& F, int64_t tile, int lane,
                                           const f32x4 (&acc)[3][BOrd<N>::RT],
-                                          const f32x4 (&m0)[3][2], float* sr, bf16x8* srl) {
+                                          const f32x4 (&m0)[3][2], float* sr, bf16x8* srl,
+                                          bf16x8* srl2) {
   using O = BOrd<N>;
   constexpr int Np = O::Np, RT = O::RT, QT = O::QT, QC = O::QC, SVQ = O::SVQ;
   constexpr int NC = wave_ncomp(W);
@@ -284,9 +368,14 @@ __device__ __forceinline__ void quad_proj(const BxArgs& A, int64_t tile, int lan
 
   // V_q B operands: K slot 8 g + j of step s holds row 4 g + j % 4 of node
   // tile 2 s + j / 4, which is where this lane's accumulator already has it.
-  // The three-component wave parks them in LDS (register budget).
+  // The three-component wave parks two parts in LDS (register budget), and the
+  // third part of FP32 over the impedances where they are large enough.
   constexpr bool park = (NC == 3);
-  bf16x8 rh[NC][SVQ], rl[NC][SVQ];
+  constexpr int PK = !park ? 0 : P == 3 && BLds<N>::PARK3 ? 3 : 2;   // parts parked
+  auto pk = [&](int i, int s, int h) {
+    return h < 2 ? srl + ((i * SVQ + s) * 2 + h) * 64 + lane : srl2 + (i * SVQ + s) * 64 + lane;
+  };
+  bf16x8 r[NC][SVQ][P];
 #pragma unroll
   for (int i = 0; i < NC; ++i)
 #pragma unroll
@@ -297,11 +386,9 @@ __device__ __forceinline__ void quad_proj(const BxArgs& A, int64_t tile, int lan
         const int t = 2 * s + j / 4;
         v[j] = t < RT ? acc[i][t][j % 4] : 0.f;
       }
-      split8(v, rh[i][s], rl[i][s]);
-      if constexpr (park) {
-        srl[((i * SVQ + s) * 2 + 0) * 64 + lane] = rh[i][s];
-        srl[((i * SVQ + s) * 2 + 1) * 64 + lane] = rl[i][s];
-      }
+      split8<P>(v, r[i][s]);
+#pragma unroll
+      for (int h = 0; h < PK; ++h) *pk(i, s, h) = r[i][s][h];
     }
 
   f32x4 out[NC][RT];
@@ -312,28 +399,37 @@ __device__ __forceinline__ void quad_proj(const BxArgs& A, int64_t tile, int lan
 
   // V_q fragments of chunk 0; inside the loop the P_q fragments and the next
   // chunk's material are issued at the top of a chunk, the next chunk's V_q
-  // fragments after its V_q products, so every fetch is covered by MFMA work
-  u32x4 fv[2][SVQ][2];
-#pragma unroll
-  for (int u = 0; u < 2; ++u)
+  // fragments after its V_q products, so every fetch is covered by MFMA work.
+  // With three parts (registers) the V_q fragments come one quadrature tile
+  // ahead and the P_q fragments after the V_q products.
+  constexpr int FU = P == 3 ? 1 : 2;   // quadrature tiles of V_q fragments held
+  u32x4 fv[2][SVQ][P];
+  auto load_v = [&](int qt, u32x4(&f)[SVQ][P]) {
 #pragma unroll
     for (int s = 0; s < SVQ; ++s)
 #pragma unroll
-      for (int h = 0; h < 2; ++h)
-        fv[u][s][h] = u < QT ? A.frags[(O::OFF_Q + (u * SVQ + s) * 2 + h) * 64 + lane]
-                             : u32x4{0u, 0u, 0u, 0u};
+      for (int h = 0; h < P; ++h)
+        f[s][h] = qt < QT ? F.load((O::OFF_Q + qt * SVQ + s) * P + h)
+                          : u32x4{0u, 0u, 0u, 0u};
+  };
+#pragma unroll
+  for (int u = 0; u < FU; ++u) load_v(u, fv[u]);
   f32x4 m[3][2];
 #pragma unroll
   for (int f = 0; f < 3; ++f) m[f][0] = m0[f][0], m[f][1] = m0[f][1];
 #pragma unroll
   for (int ch = 0; ch < QC; ++ch) {
-    u32x4 fp[RT][2];
+    u32x4 fp[RT][P];
+    auto load_p = [&]() {
 #pragma unroll
-    for (int t = 0; t < RT; ++t)
+      for (int t = 0; t < RT; ++t)
 #pragma unroll
-      for (int h = 0; h < 2; ++h) fp[t][h] = A.frags[(O::OFF_P + (t * QC + ch) * 2 + h) * 64 + lane];
+        for (int h = 0; h < P; ++h)
+          fp[t][h] = F.load((O::OFF_P + t * QC + ch) * P + h);
+    };
+    if (P == 2) load_p();
     f32x4 mn[3][2];
-    if (ch + 1 < QC) mat_chunk<N, W>(A, tile, lane, ch + 1, mn);
+    if (P == 2 && ch + 1 < QC) mat_chunk<N, W>(A, tile, lane, ch + 1, mn);
     __builtin_amdgcn_sched_barrier(0);
     const f32x4* mi = m[0];
     const f32x4* ml = m[1];
@@ -341,31 +437,46 @@ __device__ __forceinline__ void quad_proj(const BxArgs& A, int64_t tile, int lan
     f32x4 w[NC][2];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
+      if (P == 3) {
+        // the next tile's fragments (of the next chunk after u = 1)
+        if (2 * ch + u + 1 < QT) load_v(2 * ch + u + 1, fv[(u + 1) & 1]);
+        if (u == 1) load_p();
+        __builtin_amdgcn_sched_barrier(0);
+      }
 #pragma unroll
       for (int i = 0; i < NC; ++i) w[i][u] = f32x4{0.f, 0.f, 0.f, 0.f};
       if (2 * ch + u < QT) {
 #pragma unroll
-        for (int s = 0; s < SVQ; ++s)
+        for (int s = 0; s < SVQ; ++s) {
 #pragma unroll
           for (int i = 0; i < NC; ++i) {
-            if constexpr (park)
-              w[i][u] = mma3(fv[u][s][0], fv[u][s][1], srl[((i * SVQ + s) * 2 + 0) * 64 + lane],
-                             srl[((i * SVQ + s) * 2 + 1) * 64 + lane], w[i][u]);
-            else
-              w[i][u] = mma3(fv[u][s][0], fv[u][s][1], rh[i][s], rl[i][s], w[i][u]);
+#pragma unroll
+            for (int h = 0; h < PK; ++h) r[i][s][h] = *pk(i, s, h);
+            if constexpr (P == 2) {
+              w[i][u] = mma_split<P>(fv[u][s], r[i][s], w[i][u]);
+            } else {
+#pragma unroll
+              for (int k = 0; k + 1 < kProd<P>; ++k)
+                w[i][u] = mma(fv[u][s][prod_a(P, k)], r[i][s][prod_b(P, k)], w[i][u]);
+            }
           }
+          if (PK == 3) __builtin_amdgcn_sched_barrier(0);   // parked parts one step at a time
+        }
+        if constexpr (P == 3) {   // the leading products after the small ones of every step
+#pragma unroll
+          for (int s = 0; s < SVQ; ++s)
+#pragma unroll
+            for (int i = 0; i < NC; ++i) {
+              if (PK > 0) r[i][s][0] = *pk(i, s, 0);
+              w[i][u] = mma(fv[u][s][0], r[i][s][0], w[i][u]);
+            }
+        }
       }
+      if (P == 3) __builtin_amdgcn_sched_barrier(0);
     }
-    if (ch + 1 < QC) {
+    if (P == 2 && ch + 1 < QC) {
 #pragma unroll
-      for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int s = 0; s < SVQ; ++s)
-#pragma unroll
-          for (int h = 0; h < 2; ++h)
-            fv[u][s][h] = 2 * (ch + 1) + u < QT
-                              ? A.frags[(O::OFF_Q + ((2 * (ch + 1) + u) * SVQ + s) * 2 + h) * 64 + lane]
-                              : u32x4{0u, 0u, 0u, 0u};
+      for (int u = 0; u < 2; ++u) load_v(2 * (ch + 1) + u, fv[u]);
     }
     __builtin_amdgcn_sched_barrier(0);
     // pointwise weight-adjusted material operator
@@ -387,21 +498,23 @@ __device__ __forceinline__ void quad_proj(const BxArgs& A, int64_t tile, int lan
         w[1][u] *= 2.f * mm[u];
       }
     }
+    // three parts: the next chunk's material over this one's (registers)
+    if (P == 3 && ch + 1 < QC) mat_chunk<N, W>(A, tile, lane, ch + 1, m);
     // P_q B operands: K slot 8 g + j of chunk ch is row 4 g + j % 4 of
     // quadrature tile 2 ch + j / 4
-    bf16x8 ph[NC], pl[NC];
+    bf16x8 p[NC][P];
 #pragma unroll
     for (int i = 0; i < NC; ++i) {
       float v[8];
 #pragma unroll
       for (int j = 0; j < 8; ++j) v[j] = w[i][j / 4][j % 4];
-      split8(v, ph[i], pl[i]);
+      split8<P>(v, p[i]);
     }
 #pragma unroll
     for (int t = 0; t < RT; ++t)
 #pragma unroll
-      for (int i = 0; i < NC; ++i) out[i][t] = mma3(fp[t][0], fp[t][1], ph[i], pl[i], out[i][t]);
-    if (ch + 1 < QC) {
+      for (int i = 0; i < NC; ++i) out[i][t] = mma_split<P, false>(fp[t], p[i], out[i][t]);
+    if (P == 2 && ch + 1 < QC) {
 #pragma unroll
       for (int f = 0; f < 3; ++f) m[f][0] = mn[f][0], m[f][1] = mn[f][1];
     }
@@ -432,7 +545,7 @@ __device__ __forceinline__ double rcp_t(double x) { return 1.0 / x; }
 // 16 t + 4 g + j of r_{comp i}, one K slot per lane and step (the order of
 // FOrd); operator fragments are fetched one group of four steps ahead.
 template <int N, int W, typename T>
-__device__ __forceinline__ void vol_lift_f(const BxArgsT<T>& A, const T* sq, const T* sg,
+__device__ __forceinline__ void vol_lift_f(const FragBufF<T>& F, const T* sq, const T* sg,
                                            const T* sF, int lane,
                                            v4_t<T> (&acc)[3][BOrd<N>::RT]) {
   using O = FOrd<N>;
@@ -440,7 +553,6 @@ __device__ __forceinline__ void vol_lift_f(const BxArgsT<T>& A, const T* sq, con
   constexpr int Np = O::Np, NF4 = O::NF4, RT = O::RT, NB = O::NB, SV = O::SV, SV4 = O::SV4;
   constexpr int NC = wave_ncomp(W);
   const int e = lane & 15, g = lane >> 4;
-  const V4* fr = reinterpret_cast<const V4*>(A.frags) + O::OFF_V;
   T G[9];
 #pragma unroll
   for (int i = 0; i < 9; ++i) G[i] = sg[e * 9 + i];
@@ -450,12 +562,12 @@ __device__ __forceinline__ void vol_lift_f(const BxArgsT<T>& A, const T* sq, con
     for (int t = 0; t < RT; ++t) acc[i][t] = V4{0, 0, 0, 0};
   V4 fc[RT], fn[RT];
 #pragma unroll
-  for (int t = 0; t < RT; ++t) fc[t] = fr[(t * SV4) * 64 + lane];
+  for (int t = 0; t < RT; ++t) fc[t] = F.load(O::OFF_V / 64 + t * SV4);
 #pragma unroll
   for (int q = 0; q < SV4; ++q) {
     if (q + 1 < SV4) {
 #pragma unroll
-      for (int t = 0; t < RT; ++t) fn[t] = fr[(t * SV4 + q + 1) * 64 + lane];
+      for (int t = 0; t < RT; ++t) fn[t] = F.load(O::OFF_V / 64 + t * SV4 + q + 1);
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -520,7 +632,7 @@ __device__ __forceinline__ void store_raw(const BxArgs& A, int64_t e0, int ne, i
 // P_q with the weighted values as the B operand (K step (u, j) is point
 // 16 u + 4 g + j); the nodal result goes to sr.
 template <int N, int W, typename T>
-__device__ __forceinline__ void quad_proj_f(const BxArgsT<T>& A, int64_t tile, int lane,
+__device__ __forceinline__ void quad_proj_f(const BxArgsT<T>& A, const FragBufF<T>& F, int64_t tile, int lane,
                                             const v4_t<T> (&acc)[3][BOrd<N>::RT],
                                             const v4_t<T> (&m0)[3][2], T* sr) {
   using O = FOrd<N>;
@@ -528,8 +640,6 @@ __device__ __forceinline__ void quad_proj_f(const BxArgsT<T>& A, int64_t tile, i
   constexpr int Np = O::Np, RT = O::RT, QT = O::QT, QC = O::QC;
   constexpr int NC = wave_ncomp(W);
   const int e = lane & 15, g = lane >> 4;
-  const V4* frq = reinterpret_cast<const V4*>(A.frags) + O::OFF_Q;
-  const V4* frp = reinterpret_cast<const V4*>(A.frags) + O::OFF_P;
   V4 out[NC][RT];
 #pragma unroll
   for (int i = 0; i < NC; ++i)
@@ -546,8 +656,8 @@ __device__ __forceinline__ void quad_proj_f(const BxArgsT<T>& A, int64_t tile, i
       const int qt = 2 * ch + u < QT ? 2 * ch + u : QT - 1;
 #pragma unroll
       for (int t = 0; t < RT; ++t) {
-        fv[u][t] = frq[(qt * RT + t) * 64 + lane];
-        fp[t][u] = frp[(t * QT + qt) * 64 + lane];
+        fv[u][t] = F.load(O::OFF_Q / 64 + qt * RT + t);
+        fp[t][u] = F.load(O::OFF_P / 64 + t * QT + qt);
       }
     }
     V4 mn[3][2];
@@ -647,10 +757,16 @@ struct TileMap {
   }
 };
 
+// FP32 products: three bf16 parts at orders 3 and 4, where they are 1.3 times
+// faster a stage; at orders 1 and 2 the contractions are short and the splits
+// cost more than the FP32 products they replace (3,072 elements: order 1 5.0 us
+// against 5.8, order 2 7.8 against 8.3)
+constexpr bool bx_three_parts(int N) { return N >= 3; }
+
 // The stage of one tile: launch position bid of a grid of G positions over
 // the context's tiles (G = ceil(K / 16)); the kernels below call it for a
 // single context or for one slot of a batch.
-template <int N, bool F32, typename T = float, bool RST = false>
+template <int N, bool F32, typename T = float, bool RST = false, bool FP = false>
 __device__ __forceinline__ void stage_bx_run(const BxArgsT<T>& A, int64_t G, int64_t bid) {
   static_assert(F32 || sizeof(T) == 4, "BF16x3 products work on FP32 data");
   static_assert(!RST || (F32 && sizeof(T) == 4), "R q is stored by the FP32 kernel");
@@ -665,6 +781,7 @@ __device__ __forceinline__ void stage_bx_run(const BxArgsT<T>& A, int64_t G, int
   T* sF = smem + L::OFF_U;        // [9][NF4][17]  (phases B, C)
   T* sr = sF;                     // [9][Np][17]   (phases D, E)
   bf16x8* srl = reinterpret_cast<bf16x8*>(sF + L::RO);   // wave 2, phase D
+  bf16x8* srl2 = reinterpret_cast<bf16x8*>(smem + L::OFF_P3);
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -863,49 +980,43 @@ __device__ __forceinline__ void stage_bx_run(const BxArgsT<T>& A, int64_t G, int
   }
   __syncthreads();
 
-  // C: volume + LIFT per wave
+  // C: volume + LIFT per wave (BF16x3 in two bf16 parts, FP32 in three or on the
+  // FP32 products, FP64 on the FP64 products)
   V4 acc[3][RT];
   V4 m0[3][2];   // chunk-0 material, in flight during phase C
-  if constexpr (F32) {
-    switch (grp) {
-      case 0: mat_chunk<N, 0, T>(A, tile, lane, 0, m0); vol_lift_f<N, 0, T>(A, sq, sg, sF, lane, acc); break;
-      case 1: mat_chunk<N, 1, T>(A, tile, lane, 0, m0); vol_lift_f<N, 1, T>(A, sq, sg, sF, lane, acc); break;
-      case 2: mat_chunk<N, 2, T>(A, tile, lane, 0, m0); vol_lift_f<N, 2, T>(A, sq, sg, sF, lane, acc); break;
-      default: mat_chunk<N, 3, T>(A, tile, lane, 0, m0); vol_lift_f<N, 3, T>(A, sq, sg, sF, lane, acc); break;
-    }
-    if constexpr (RST) {
-      switch (grp) {
-        case 0: store_raw<N, 0>(A, e0, ne, lane, acc); break;
-        case 1: store_raw<N, 1>(A, e0, ne, lane, acc); break;
-        case 2: store_raw<N, 2>(A, e0, ne, lane, acc); break;
-        default: store_raw<N, 3>(A, e0, ne, lane, acc); break;
-      }
-    }
-  } else {
-    switch (grp) {
-      case 0: mat_chunk<N, 0>(A, tile, lane, 0, m0); vol_lift<N, 0>(A, sq, sg, sF, lane, acc); break;
-      case 1: mat_chunk<N, 1>(A, tile, lane, 0, m0); vol_lift<N, 1>(A, sq, sg, sF, lane, acc); break;
-      case 2: mat_chunk<N, 2>(A, tile, lane, 0, m0); vol_lift<N, 2>(A, sq, sg, sF, lane, acc); break;
-      default: mat_chunk<N, 3>(A, tile, lane, 0, m0); vol_lift<N, 3>(A, sq, sg, sF, lane, acc); break;
-    }
+  constexpr int P = F32 ? 3 : 2;
+  constexpr bool plain = sizeof(T) == 8 || FP || (F32 && !bx_three_parts(N));   // FOrd fragments
+  const FragBuf F(A.frags, O::NFRAG * P, lane);   // split products
+  const FragBufF<T> FF(A.frags, FOrd<N>::NF4S, lane);
+  auto phase_c = [&](auto w) {
+    constexpr int W = decltype(w)::value;
+    // FP32: after the products (registers)
+    constexpr bool late = P == 3 && !plain;
+    if constexpr (!late) mat_chunk<N, W, T>(A, tile, lane, 0, m0);
+    if constexpr (plain) vol_lift_f<N, W, T>(FF, sq, sg, sF, lane, acc);
+    else vol_lift<N, W, P>(A, F, sq, sg, sF, lane, acc);
+    if constexpr (late) mat_chunk<N, W, T>(A, tile, lane, 0, m0);
+    if constexpr (RST) store_raw<N, W>(A, e0, ne, lane, acc);
+  };
+  switch (grp) {
+    case 0: phase_c(std::integral_constant<int, 0>()); break;
+    case 1: phase_c(std::integral_constant<int, 1>()); break;
+    case 2: phase_c(std::integral_constant<int, 2>()); break;
+    default: phase_c(std::integral_constant<int, 3>()); break;
   }
   __syncthreads();   // fluxes consumed: sr may overwrite them
 
   // D: quadrature and projection per wave
-  if constexpr (F32) {
-    switch (grp) {
-      case 0: quad_proj_f<N, 0, T>(A, tile, lane, acc, m0, sr); break;
-      case 1: quad_proj_f<N, 1, T>(A, tile, lane, acc, m0, sr); break;
-      case 2: quad_proj_f<N, 2, T>(A, tile, lane, acc, m0, sr); break;
-      default: quad_proj_f<N, 3, T>(A, tile, lane, acc, m0, sr); break;
-    }
-  } else {
-    switch (grp) {
-      case 0: quad_proj<N, 0>(A, tile, lane, acc, m0, sr, srl); break;
-      case 1: quad_proj<N, 1>(A, tile, lane, acc, m0, sr, srl); break;
-      case 2: quad_proj<N, 2>(A, tile, lane, acc, m0, sr, srl); break;
-      default: quad_proj<N, 3>(A, tile, lane, acc, m0, sr, srl); break;
-    }
+  auto phase_d = [&](auto w) {
+    constexpr int W = decltype(w)::value;
+    if constexpr (plain) quad_proj_f<N, W, T>(A, FF, tile, lane, acc, m0, sr);
+    else quad_proj<N, W, P>(A, F, tile, lane, acc, m0, sr, srl, srl2);
+  };
+  switch (grp) {
+    case 0: phase_d(std::integral_constant<int, 0>()); break;
+    case 1: phase_d(std::integral_constant<int, 1>()); break;
+    case 2: phase_d(std::integral_constant<int, 2>()); break;
+    default: phase_d(std::integral_constant<int, 3>()); break;
   }
 
   // E: right-hand side store or fused stage update, coalesced, done by the
@@ -954,19 +1065,33 @@ __device__ __forceinline__ void stage_bx_run(const BxArgsT<T>& A, int64_t G, int
   }
 }
 
+// waves per SIMD that registers have to allow: LDS holds two workgroups per CU at
+// order 4, three at orders 1-3 (order 3 would take 171 registers, three more than
+// three workgroups leave)
+constexpr int bx_waves(int N) { return N == 3 ? 3 : 2; }
+
 template <int N, bool F32>
-__global__ __launch_bounds__(kThreads, 2) void stage_bx(BxArgs A) {
+__global__ __launch_bounds__(kThreads, bx_waves(N)) void stage_bx(BxArgs A) {
   stage_bx_run<N, F32>(A, gridDim.x, blockIdx.x);
 }
 
-// The FP32 stage that also stores the raw right-hand side R q of its input
+// The FP32 stage on FP32 products at every order (FOrd fragments): the forward
+// run and the replay of the discrete adjoint.  The face-node jumps that its
+// gradients are made of cancel to 1e-5 of the state, so that another rounding of
+// the states changes an FP32 gradient by 1e-5 to 1e-3 of its norm, as much as its
+// own error; the adjoint therefore keeps these products in all of its parts.
+template <int N>
+__global__ __launch_bounds__(kThreads, 2) void stage_bx_p(BxArgs A) {
+  stage_bx_run<N, true, float, false, true>(A, gridDim.x, blockIdx.x);
+}
+
+// The same stage that also stores the raw right-hand side R q of its input
 // (r_out) and, for the upwind flux, the jumps at its face nodes (j_out): the
-// replay of a checkpoint interval in the discrete adjoint, whose reverse
-// stage needs R y of every stage input and, for the impedance gradient, its
-// face-node jumps
+// replay of a checkpoint interval, whose reverse stage needs R y of every stage
+// input and, for the impedance gradient, its face-node jumps
 template <int N>
 __global__ __launch_bounds__(kThreads, 2) void stage_bx_r(BxArgs A) {
-  stage_bx_run<N, true, float, true>(A, gridDim.x, blockIdx.x);
+  stage_bx_run<N, true, float, true, true>(A, gridDim.x, blockIdx.x);
 }
 
 // FP64 stage on the matrix cores (v_mfma_f64_16x16x4f64): the FP32 kernel's

@@ -43,12 +43,13 @@ struct BOrd {
   static constexpr int QT = (Nq + 15) / 16;         // 16-row quadrature tiles
   static constexpr int QC = (QT + 1) / 2;           // K steps of P_q (32 points each)
   static constexpr int SVQ = (RT + 1) / 2;          // K steps of V_q
-  // fragments of 64 lanes x 8 bf16; hi and lo of one (tile, step) adjacent
-  static constexpr int NFV = RT * SVL * 2;
-  static constexpr int NFQ = QT * SVQ * 2;
-  static constexpr int NFP = RT * QC * 2;
+  // fragments of 64 lanes x 8 bf16: the P parts of (tile, step) index i at
+  // P i ... (two parts for BF16x3, three for FP32)
+  static constexpr int NFV = RT * SVL;
+  static constexpr int NFQ = QT * SVQ;
+  static constexpr int NFP = RT * QC;
   static constexpr int OFF_V = 0, OFF_Q = NFV, OFF_P = NFV + NFQ;
-  static constexpr int NFRAG = NFV + NFQ + NFP;
+  static constexpr int NFRAG = NFV + NFQ + NFP;   // times P
   // blocked material: floats per (element tile, field)
   static constexpr int MATS = QC * 2 * 64 * 4;
 };

@@ -17,6 +17,8 @@ namespace dgl {
 template <int N, bool F32>
 hipError_t stage_bx(const dgb::BxArgs& A, unsigned grid, hipStream_t st);
 template <int N>
+hipError_t stage_bx_p(const dgb::BxArgs& A, unsigned grid, hipStream_t st);
+template <int N>
 hipError_t stage_bx_r(const dgb::BxArgs& A, unsigned grid, hipStream_t st);
 template <int N>
 hipError_t stage_bx_d(const dgb::BxArgsT<double>& A, unsigned grid, hipStream_t st);

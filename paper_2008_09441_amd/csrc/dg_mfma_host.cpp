@@ -23,28 +23,29 @@ float bf16_val(uint16_t h) {
 
 // Operator fragments in MFMA A-operand lane order: fragment (t, s, h) holds,
 // for lane l, the operator entries of row 16 t + l % 16 at the K slots
-// 8 (l / 16) + j, j = 0..7, of K step s, as h = 0: hi = bf16(a), h = 1:
-// lo = bf16(a - hi).  The meaning of each K slot (which node, direction,
+// 8 (l / 16) + j, j = 0..7, of K step s, part h the bf16 rounding of what the
+// parts before it leave.  The meaning of each K slot (which node, direction,
 // face node or quadrature point it carries) is the permutation described with
 // the kernel's sizes; rows and slots beyond the element's counts are zero.
-template <int N>
+template <int N, int P>
 std::vector<uint16_t> build_frags(const RefElement& re) {
   using O = dgb::BOrd<N>;
-  std::vector<uint16_t> out(size_t(O::NFRAG) * 64 * 8, 0);
+  std::vector<uint16_t> out(size_t(O::NFRAG) * P * 64 * 8, 0);
   auto put = [&](int frag, auto&& aval) {   // aval(row offset in tile, g, j)
     for (int l = 0; l < 64; ++l)
       for (int j = 0; j < 8; ++j) {
-        const double v = aval(l % 16, l / 16, j);
-        const uint16_t hi = bf16_rne(float(v));
-        const uint16_t lo = bf16_rne(float(v - double(bf16_val(hi))));
-        out[(size_t(frag) * 64 + l) * 8 + j] = hi;
-        out[(size_t(frag + 1) * 64 + l) * 8 + j] = lo;
+        double v = aval(l % 16, l / 16, j);
+        for (int p = 0; p < P; ++p) {
+          const uint16_t h = bf16_rne(float(v));
+          out[(size_t(frag * P + p) * 64 + l) * 8 + j] = h;
+          v -= double(bf16_val(h));
+        }
       }
   };
   const int Np = O::Np, NF4 = O::NF4, Nq = O::Nq;
   for (int t = 0; t < O::RT; ++t)
     for (int s = 0; s < O::SVL; ++s)
-      put(O::OFF_V + (t * O::SVL + s) * 2, [&](int r, int g, int j) -> double {
+      put(O::OFF_V + t * O::SVL + s, [&](int r, int g, int j) -> double {
         const int n = 16 * t + r;
         if (n >= Np) return 0.0;
         if (s < O::SN && j < 6) {
@@ -59,14 +60,14 @@ std::vector<uint16_t> build_frags(const RefElement& re) {
       });
   for (int t = 0; t < O::QT; ++t)
     for (int s = 0; s < O::SVQ; ++s)
-      put(O::OFF_Q + (t * O::SVQ + s) * 2, [&](int r, int g, int j) -> double {
+      put(O::OFF_Q + t * O::SVQ + s, [&](int r, int g, int j) -> double {
         const int p = 16 * t + r;
         const int n = 16 * (2 * s + j / 4) + 4 * g + j % 4;
         return (p < Nq && n < Np) ? re.Vq[size_t(p) * Np + n] : 0.0;
       });
   for (int t = 0; t < O::RT; ++t)
     for (int c = 0; c < O::QC; ++c)
-      put(O::OFF_P + (t * O::QC + c) * 2, [&](int r, int g, int j) -> double {
+      put(O::OFF_P + t * O::QC + c, [&](int r, int g, int j) -> double {
         const int n = 16 * t + r;
         const int p = 32 * c + 16 * (j / 4) + 4 * g + j % 4;
         return (n < Np && p < Nq) ? re.Pq[size_t(n) * Nq + p] : 0.0;
@@ -74,8 +75,8 @@ std::vector<uint16_t> build_frags(const RefElement& re) {
   return out;
 }
 
-// Fragments of the FP32 / FP64 matrix-core stage (FOrd) in the working
-// precision V, four steps per lane
+// Fragments of the FP32 (orders 1, 2) and FP64 matrix-core stage (FOrd) in the
+// working precision V, four steps per lane
 template <int N, typename V>
 std::vector<V> build_frags_f(const RefElement& re) {
   using O = dgb::FOrd<N>;
@@ -190,10 +191,10 @@ bool mfma_supported(int N) { return N >= 1 && N <= 7; }
 
 std::vector<uint16_t> mfma_fragments(const RefElement& re) {
   switch (re.N) {
-    case 1: return build_frags<1>(re);
-    case 2: return build_frags<2>(re);
-    case 3: return build_frags<3>(re);
-    case 4: return build_frags<4>(re);
+    case 1: return build_frags<1, 2>(re);
+    case 2: return build_frags<2, 2>(re);
+    case 3: return build_frags<3, 2>(re);
+    case 4: return build_frags<4, 2>(re);
     case 5: return build_frags_e<5, 2>(re);
     case 6: return build_frags_e<6, 2>(re);
     default: return build_frags_e<7, 2>(re);
@@ -202,16 +203,16 @@ std::vector<uint16_t> mfma_fragments(const RefElement& re) {
 
 std::vector<uint16_t> mfma_fragments_bf16x6(const RefElement& re) {
   switch (re.N) {
-    case 3: return build_frags_e<3, 3>(re);
-    case 4: return build_frags_e<4, 3>(re);
+    case 3: return build_frags<3, 3>(re);
+    case 4: return build_frags<4, 3>(re);
     case 5: return build_frags_e<5, 3>(re);
     case 6: return build_frags_e<6, 3>(re);
     default: return {};
   }
 }
 
-// FP32 (V = float) or FP64 (V = double) fragments of the orders 5-7 stage in
-// the layout of EFOrd
+// FP32 (V = float) or FP64 (V = double) fragments of the one-element
+// stage in the layout of EFOrd
 template <int N, typename V>
 std::vector<V> build_frags_ef(const RefElement& re) {
   using O = dgb::EFOrd<N>;
@@ -239,6 +240,16 @@ std::vector<V> build_frags_ef(const RefElement& re) {
   return out;
 }
 
+std::vector<float> mfma_fragments_f32(const RefElement& re) {
+  switch (re.N) {
+    case 1: return build_frags_f<1, float>(re);
+    case 2: return build_frags_f<2, float>(re);
+    case 3: return build_frags_f<3, float>(re);
+    case 4: return build_frags_f<4, float>(re);
+    default: return {};
+  }
+}
+
 std::vector<uint16_t> element_fragments(const RefElement& re) {
   switch (re.N) {
     case 1: return build_frags_e<1, 2>(re);
@@ -255,7 +266,9 @@ std::vector<float> element_fragments_f32(const RefElement& re) {
     case 2: return build_frags_ef<2, float>(re);
     case 3: return build_frags_ef<3, float>(re);
     case 4: return build_frags_ef<4, float>(re);
-    default: return mfma_fragments_f32(re);
+    case 5: return build_frags_ef<5, float>(re);
+    case 6: return build_frags_ef<6, float>(re);
+    default: return build_frags_ef<7, float>(re);
   }
 }
 
@@ -266,18 +279,6 @@ std::vector<double> element_fragments_f64(const RefElement& re) {
     case 3: return build_frags_ef<3, double>(re);
     case 4: return build_frags_ef<4, double>(re);
     default: return mfma_fragments_f64(re);
-  }
-}
-
-std::vector<float> mfma_fragments_f32(const RefElement& re) {
-  switch (re.N) {
-    case 1: return build_frags_f<1, float>(re);
-    case 2: return build_frags_f<2, float>(re);
-    case 3: return build_frags_f<3, float>(re);
-    case 4: return build_frags_f<4, float>(re);
-    case 5: return build_frags_ef<5, float>(re);
-    case 6: return build_frags_ef<6, float>(re);
-    default: return build_frags_ef<7, float>(re);
   }
 }
 
@@ -324,10 +325,10 @@ std::vector<double> mfma_material(int N, int64_t K, const double* irho, const do
 
 int mfma_frag_count(int N) {
   switch (N) {
-    case 1: return dgb::BOrd<1>::NFRAG;
-    case 2: return dgb::BOrd<2>::NFRAG;
-    case 3: return dgb::BOrd<3>::NFRAG;
-    case 4: return dgb::BOrd<4>::NFRAG;
+    case 1: return 2 * dgb::BOrd<1>::NFRAG;
+    case 2: return 2 * dgb::BOrd<2>::NFRAG;
+    case 3: return 2 * dgb::BOrd<3>::NFRAG;
+    case 4: return 2 * dgb::BOrd<4>::NFRAG;
     case 5: return dgb::EOrd<5>::NFRAG;
     case 6: return dgb::EOrd<6>::NFRAG;
     default: return dgb::EOrd<7>::NFRAG;
@@ -409,7 +410,7 @@ int element_frag_count(int N, bool split) {
   }
 }
 
-int mfma_f32_frag_count(int N) {
+int mfma_f64_frag_count(int N) {
   switch (N) {
     case 1: return dgb::FOrd<1>::NF4S;
     case 2: return dgb::FOrd<2>::NF4S;

@@ -18,24 +18,21 @@ bool mfma_supported(int N);
 // lanes][8]
 std::vector<uint16_t> mfma_fragments(const RefElement& re);
 
-// the same operators in three bf16 parts, in the layout of the BF16x3
-// fragments of orders 5-7 with three parts per fragment: the FP32 stage on
-// 16-element tiles (orders 5 and 6; empty at the others)
+// FP32 tiles: the same operators in three bf16 parts (orders 3-6, the layout of
+// mfma_fragments with three parts per fragment; empty at the others), and FP32
+// fragments in the layout of FOrd ([NF4S][4] floats: orders 1-4, which the stage
+// of orders 1 and 2 and the adjoint's stages take; empty at the others)
 std::vector<uint16_t> mfma_fragments_bf16x6(const RefElement& re);
+std::vector<float> mfma_fragments_f32(const RefElement& re);
 
 // fragments of the one-element-per-workgroup stage, which small meshes run at
 // every order: BF16x3 in the layout of EOrd, FP32 and FP64 in that of EFOrd
-// (at orders 5-7 those of mfma_fragments, _f32 and _f64)
+// (at orders 5-7 BF16x3 and FP64 are those of mfma_fragments and _f64)
 std::vector<uint16_t> element_fragments(const RefElement& re);
 std::vector<float> element_fragments_f32(const RefElement& re);
 std::vector<double> element_fragments_f64(const RefElement& re);
 // their count at order N (of 64 lanes; split: hi and lo of EOrd, else EFOrd)
 int element_frag_count(int N, bool split);
-
-// FP32 operator fragments of the FP32 matrix-core stage: orders 1-4 in the
-// layout of FOrd ([NF4S][4] floats), orders 5-7 in that of EFOrd
-// ([NFRAG][64 lanes][4] floats)
-std::vector<float> mfma_fragments_f32(const RefElement& re);
 
 // FP64 operator fragments of the FP64 matrix-core stage: orders 1-4 in the
 // layout of FOrd ([NF4S][4] doubles), orders 5-7 in that of EFOrd
@@ -59,8 +56,8 @@ std::vector<double> mfma_material(int N, int64_t K, const double* irho, const do
 
 // fragment count and blocked-material floats per (tile, field) of order N
 int mfma_frag_count(int N);
-// float4 count of the FP32 fragments of order N (1-7)
-int mfma_f32_frag_count(int N);
+// four-value count of the FP64 fragments of order N (1-7)
+int mfma_f64_frag_count(int N);
 int mfma_mats(int N);
 
 // index in the blocked material array of field f (0 1/rho, 1 lam, 2 mu) at

@@ -15,6 +15,12 @@ hipError_t stage_bx(const dgb::BxArgs& A, unsigned grid, hipStream_t st) {
 }
 
 template <int N>
+hipError_t stage_bx_p(const dgb::BxArgs& A, unsigned grid, hipStream_t st) {
+  dgb::stage_bx_p<N><<<dim3(grid), dim3(dgb::kThreads), 0, st>>>(A);
+  return hipGetLastError();
+}
+
+template <int N>
 hipError_t stage_bx_r(const dgb::BxArgs& A, unsigned grid, hipStream_t st) {
   dgb::stage_bx_r<N><<<dim3(grid), dim3(dgb::kThreads), 0, st>>>(A);
   return hipGetLastError();
@@ -72,8 +78,8 @@ hipError_t stage_batch(const dgb::BatchSlot* table, int n, unsigned grid, bool t
   return hipGetLastError();
 }
 
-// DG_PART picks the kernels of a unit: 0 BF16x3, 1 FP32, 2 FP64, 3 the tiled
-// adjoint and its replay stage
+// DG_PART picks the kernels of a unit: 0 BF16x3, 1 FP32, 2 FP64, 3 the stages
+// and the tile kernel of the adjoint
 #define DG_INST template hipError_t
 #if DG_PART < 2
 DG_INST stage_batch<DG_ORDER, DG_PART == 1>(const dgb::BatchSlot*, int, unsigned, bool, hipStream_t,
@@ -90,6 +96,7 @@ DG_INST stage_bx<DG_ORDER, DG_PART == 1>(const dgb::BxArgs&, unsigned, hipStream
 #elif DG_PART == 2
 DG_INST stage_bx_d<DG_ORDER>(const dgb::BxArgsT<double>&, unsigned, hipStream_t);
 #else
+DG_INST stage_bx_p<DG_ORDER>(const dgb::BxArgs&, unsigned, hipStream_t);
 DG_INST stage_bx_r<DG_ORDER>(const dgb::BxArgs&, unsigned, hipStream_t);
 DG_INST adj_tile<DG_ORDER>(const dgt::TileArgs&, unsigned, hipStream_t);
 #endif

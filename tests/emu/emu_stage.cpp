@@ -181,9 +181,9 @@ static int emu_rhs(int N, int64_t K, const double* vxyz, const double* period,
     for (int64_t i = 0; i < 9 * K * Np; ++i) A.res[i] = 0.f;
     A.lsrk = 1;
   }
-  if (f32) {
-    const std::vector<float> ff = dgh::mfma_fragments_f32(re);
-    A.frags = reinterpret_cast<const dgb::u32x4*>(dup(ff));
+  if (f32) {   // three bf16 parts (orders 1 and 2: FP32 fragments)
+    A.frags = N <= 2 || grid == 4 ? reinterpret_cast<const dgb::u32x4*>(dup(dgh::mfma_fragments_f32(re)))
+                     : reinterpret_cast<const dgb::u32x4*>(dup(dgh::mfma_fragments_bf16x6(re)));
   } else {
     A.frags = reinterpret_cast<const dgb::u32x4*>(dup(fr));
   }
