@@ -111,7 +111,7 @@ struct dg_ctx {
   DevBuf adj_nbface, adj_invf;
   DevBuf adj_ck;            // checkpoints [nck][9][K][Np]
   DevBuf adj_seg;           // stage inputs of one segment [every][5][9][K][Np]
-  DevBuf adj_v;             // ly, lres, mu, nu, r, res [6][9][K][Np]
+  DevBuf adj_v;             // ly, lres, mu, r, res [5][9][K][Np] (tiled: six, see there)
   DevBuf adj_gb, adj_hb;    // face-node work [K][4 Nfp][9]
   DevBuf adj_grad;          // double [3][K][Nq]
   DevBuf adj_zb;            // upwind: impedance terms per face node [K][4 Nfp][4]
@@ -1013,15 +1013,20 @@ dg_status adj_backward_t(dg_ctx* c, const T* resid) {
   T* ck = static_cast<T*>(c->adj_ck.p);
   T* seg = static_cast<T*>(c->adj_seg.p);
   T* v = static_cast<T*>(c->adj_v.p);
-  T *ly = v, *lres = v + n, *mu = v + 2 * n, *nu = v + 3 * n, *r = v + 4 * n, *res = v + 5 * n;
+  T *ly = v, *lres = v + n, *mu = v + 2 * n, *r = v + 3 * n, *res = v + 4 * n;
   T* gb = static_cast<T*>(c->adj_gb.p);
   T* hb = static_cast<T*>(c->adj_hb.p);
   double* grad = static_cast<double*>(c->adj_grad.p);
   // per-element kernels: one workgroup per element, the element's vectors in LDS
   if (K > 0x7fffffff) return fail(c, DG_EINVAL, "adjoint: too many elements for one grid");
   const dim3 eg(static_cast<unsigned>(K)), et(static_cast<unsigned>(dga::kAdjThreads));
-  const size_t lraw = size_t(dga::raw_lds_elems(Np, c->re.Nfp)) * sizeof(T);
-  const size_t lgw = size_t(dga::gradw_lds_elems(Np, Nq)) * sizeof(T);
+  const bool split = dga::adj_split(Np);
+  const dim3 traw(dga::adj_threads(dga::raw_s_items(Np, c->re.Nfp)));
+  const dim3 tgw(dga::adj_threads(3 * Nq));
+  const size_t lraw = size_t(split ? dga::raw_s_lds_elems(Np, c->re.Nfp)
+                                   : dga::raw_lds_elems(Np, c->re.Nfp)) * sizeof(T);
+  const size_t lgw = split ? dga::gradw_s_lds_bytes<T>(Np, Nq)
+                           : size_t(dga::gradw_lds_elems(Np, Nq)) * sizeof(T);
   const size_t l9 = size_t(9) * Np * sizeof(T);
   const double t0 = c->adj_t0, dt = c->adj_dt;
   const int64_t nsteps = c->adj_nsteps, every = c->adj_every;
@@ -1069,17 +1074,20 @@ dg_status adj_backward_t(dg_ctx* c, const T* resid) {
       const double ti = t0 + double(i) * dt;
       for (int q = 4; q >= 0; --q) {
         const double ts = ti + kRkC[q] * dt;
-        dga::axpby<T><<<nblocks(n), 256, 0, st>>>(lres, ly, kRkB[q], 1.0, n);
-        // gradient: dt d/dm <lres, W(m) (R y_q + raw sources(ts))>
-        dga::raw_rhs<T><<<eg, et, lraw, st>>>(A, ys + q * n, r);
+        // lres += b ly; gradient: dt d/dm <lres, W(m) (R y_q + raw sources(ts))>
+        if (split) dga::raw_rhs_s<T><<<eg, traw, lraw, st>>>(A, ys + q * n, r);
+        else dga::raw_rhs<T><<<eg, et, lraw, st>>>(A, ys + q * n, r);
         if (ns > 0) {
           dgs::source_add<T><<<nblocks(3 * Np), 256, 0, st>>>(
               r, static_cast<T*>(nullptr), static_cast<const int64_t*>(c->src_elem.p),
               static_cast<const T*>(c->src_wraw.p), static_cast<const double*>(c->src_par.p),
               ns, Np, KNp, ts, 1.0, 0.0);
         }
-        // and mu = W^T lres (one kernel); then ly += dt R^T mu
-        dga::grad_wadgT<T><<<eg, et, lgw, st>>>(A, lres, r, grad, dt, mu);
+        // and mu = W^T lres (one kernel, which leaves a lres); then ly += dt R^T mu
+        if (split)
+          dga::grad_wadgT_s<T><<<eg, tgw, lgw, st>>>(A, lres, ly, kRkA[q], kRkB[q], r, grad, dt, mu);
+        else
+          dga::grad_wadgT<T><<<eg, et, lgw, st>>>(A, lres, ly, kRkA[q], kRkB[q], r, grad, dt, mu);
         dga::liftT_faces<T><<<eg, et, l9, st>>>(A, mu, gb);
         if (upwind) {
           // and the impedance gradient dt d/dZ <mu, R(Z) y_q>
@@ -1087,9 +1095,7 @@ dg_status adj_backward_t(dg_ctx* c, const T* resid) {
           dga::zgrad_nodes<T><<<nblocks(KNp), 256, 0, st>>>(A, zb, gradz, dt);
         }
         dga::fluxT_faces<T><<<nblocks(K * NF4), 256, 0, st>>>(A, gb, hb);
-        dga::volT_nodes<T><<<eg, et, l9, st>>>(A, mu, hb, nu);
-        dga::axpby<T><<<nblocks(n), 256, 0, st>>>(ly, nu, dt, 1.0, n);
-        dga::axpby<T><<<nblocks(n), 256, 0, st>>>(lres, lres, 0.0, kRkA[q], n);
+        dga::volT_nodes<T><<<eg, et, l9, st>>>(A, mu, hb, dt, ly);
         DG_HIP(c, hipGetLastError());
       }
     }
@@ -2132,7 +2138,7 @@ dg_status dg_adjoint_forward(dg_ctx* c, double t0, double dt, int64_t nsteps, in
     } need[] = {{&c->adj_ck, S * nck},
                 {&c->adj_seg, segb * nseg},
                 {&c->adj_r, tiled ? segb * nseg : 0},
-                {&c->adj_v, S * 6},
+                {&c->adj_v, S * (tiled ? 6 : 5)},
                 {&c->adj_gb, size_t(K) * NF4 * 9 * c->elem},
                 {&c->adj_hb, tiled ? 0 : size_t(K) * NF4 * 9 * c->elem},
                 {&c->adj_grad, size_t(K) * Nq * 3 * sizeof(double)},
