@@ -222,11 +222,12 @@ dg_status dg_graph_advance(dg_ctx* ctx, double dt, int64_t nsteps);
 
 /* ---- Batched stepping (continuous batching of many solves) -------------
  * Many independent contexts of one order and precision advanced together:
- * each LSRK stage of the whole batch is one launch of the context's stage
- * kernel over a slot table (every context owns a range of workgroups and
- * runs the same per-tile arithmetic as alone, so each result is
- * bit-identical alone and in a batch), followed by one source launch, and
- * after each step one receiver launch, for all slots.  Each context steps
+ * each LSRK stage of the whole batch is one launch of the contexts' stage
+ * kernel over a slot table (two at orders 5-7 where some contexts run
+ * 16-element tiles and others, of few tiles, one element per workgroup; every
+ * context owns a range of workgroups and runs the same arithmetic as alone, so
+ * each result is bit-identical alone and in a batch), followed by one source
+ * launch, and after each step one receiver launch, for all slots.  Each context steps
  * on its own device clock with its own dt, exactly as dg_advance would, and
  * may join or leave the batch between calls. */
 

@@ -76,7 +76,7 @@ struct dg_ctx {
   DevBuf irho, lam, mu, zp, zs;
   DevBuf q[2], res;
   DevBuf frags;             // operator fragments of the matrix-core stages
-  DevBuf efrags;            // those of one element per workgroup (FP32, and orders 1-4)
+  DevBuf efrags;            // those of one element per workgroup (FP64 orders 2-4, FP32 5-7)
   DevBuf matblk;            // BF16x3: material blocked by 16-element tile
   DevBuf nbn;               // BF16x3: neighbour volume node of each face node
   DevBuf torder;            // BF16x3: tile processed at each launch position
@@ -155,36 +155,54 @@ bool device_ctx(const dg_ctx* c) { return c->opt.device >= 0; }
 // orders 1-4 (BF16x3, FP32 and FP64 products); it reads the blocked
 // material, the neighbour-node table and the tile order.  The [K][Nq]
 // material is held by every other context and by FP32 and FP64 ones too
-// (adjoint, sources) and by those that run one element per workgroup.
+// (adjoint, sources, one element per workgroup).
 bool tiled_kernel(int32_t precision, int order) {
   return order <= 4 &&
          (precision == DG_FP32_BF16X3 || precision == DG_FP32 || precision == DG_FP64);
 }
-// FP32 and BF16x3 contexts (launch_mfma: the tiled kernel at orders 1-4, one
-// element per workgroup at 5-7); FP64 contexts run the FP64 matrix-core
+bool plain_material(int32_t precision, int order) {
+  return !(precision == DG_FP32_BF16X3 && order <= 4);
+}
+// FP32 and BF16x3 contexts (launch_mfma: 16-element tiles at orders 1-4, tiles
+// or one element per workgroup at 5-7); FP64 contexts run the FP64 matrix-core
 // kernels through launch_stage.
 bool tiled_mfma(const dg_ctx* c) {
   return c->opt.precision == DG_FP32_BF16X3 || c->opt.precision == DG_FP32;
 }
-// Contexts of few 16-element tiles run one element per workgroup (dg_be.hpp) at
-// orders 2-7: a tile takes its whole latency however few there are and leaves
-// the other CUs idle, one element per workgroup spreads over the chip but reads
-// every operator for each element.  us per stage on both sides (tiles,
-// elements): order 2 FP32 7.0, 6.3 at 384 elements and 7.3, 7.5 at 750; order 3
-// FP64 18.4, 11.1 at 384 and 18.9, 25.0 at 1,296, BF16x3 9.3, 7.7 at 750; order
-// 4 FP64 39, 21 at 750 and 41, 52 at 2,058, BF16x3 14.6, 10.2 at 750 and 14.8,
-// 17.7 at 1,296; orders 5-7 22-48 a tile against 13-38 ns an element.  At order
-// 1 tiles are never slower.  FP64 at orders 5-7 and FP32 at order 7 have no
-// tiled kernel (a tile's data does not fit in LDS).
+// Contexts of few 16-element tiles run one element per workgroup (dg_be.hpp):
+// a tile takes its whole latency however few there are and leaves the other CUs
+// idle, one element per workgroup spreads over the chip but reads every operator
+// for each element.  The choice is a property of the context alone, so that its
+// results are the same bits alone and in a batch (dg_batch_advance).
+//   FP64 is never batched, so its lines are where one context is faster, us per
+// stage (tiles, elements): order 2 8.8, 7.0 at 162 elements; order 3 18.5, 11.3
+// at 384 and 18.6, 15.0 at 750; order 4 39.2, 15.6 at 384 and 39.6, 21.2 at 750.
+//   FP32 and BF16x3 contexts may be batched, and a batch fills the chip with
+// the tiles of all of its contexts.  At orders 2-4 an element then costs three to
+// five times as much in a workgroup of its own as in a tile (eight contexts of
+// 750 elements: order 3 64 us a stage against 22 in FP32, 51 against 16 in
+// BF16x3; order 4 89 against 44, 69 against 25), whatever one small context would
+// gain (order 4 BF16x3, 384 elements: 14.4, 8.5), so they run tiles at every size.
+//   At orders 5-7 a batch of both kinds takes two launches a stage, one after the
+// other.  The lines are where a tile context saves more than that costs beside
+// any others, us per stage with a context of 162 elements (all elements, tiles
+// and elements): BF16x3 order 5 35.6, 36.5 at 1,800 elements and 38.5, 37.5 at
+// 2,058, order 6 73.7, 76.1 at 2,304 and 80.1, 77.5 at 2,592, order 7 69.5, 76.3
+// at 1,296 and 83.2, 76.6 at 1,536; FP32 order 5 37.9, 39.0 at 1,296 and 44.4,
+// 39.2 at 1,536, order 6 92.2, 96.5 at 1,536 and 103.5, 97.1 at 1,800.
+//   At order 1 tiles are never slower.  FP64 at orders 5-7 and FP32 at order 7
+// have no tile kernel (their tiles need more than the 128 KiB of LDS that a
+// workgroup takes here).
 bool one_element(int32_t precision, int order, int64_t K) {
-  if (order >= 5 && (precision == DG_FP64 || (precision == DG_FP32 && order == 7))) return true;
-  const int64_t least[8] = {0, 0, 24, 48, 64, 72, 72, 72};   // tiles, by order
-  return (K + dgb::kTile - 1) / dgb::kTile < least[order];
+  constexpr int64_t always = INT64_MAX;
+  // tiles from which on a context runs tiles, by order 1-7
+  static constexpr int64_t fp64[] = {0, 24, 48, 64, always, always, always};
+  static constexpr int64_t fp32[] = {0, 0, 0, 0, 96, 112, always};
+  static constexpr int64_t bf16x3[] = {0, 0, 0, 0, 128, 160, 96};
+  const int64_t* least = precision == DG_FP64 ? fp64 : precision == DG_FP32 ? fp32 : bf16x3;
+  return (K + dgb::kTile - 1) / dgb::kTile < least[order - 1];
 }
 bool one_element(const dg_ctx* c) { return one_element(c->opt.precision, c->re.N, c->mesh.K); }
-bool plain_material(int32_t precision, int order, int64_t K) {
-  return !(precision == DG_FP32_BF16X3 && order <= 4) || one_element(precision, order, K);
-}
 // FP32 contexts of orders 1-4 run the reverse stage on the tiled adjoint
 // kernel (matrix cores); the others on the generic adjoint kernels
 bool adj_tiled(const dg_ctx* c) { return c->opt.precision == DG_FP32 && c->re.N <= 4; }
@@ -295,7 +313,7 @@ dgb::BeArgsT<T> be_args(const dg_ctx* c) {
   A.mu = static_cast<const T*>(c->mu.p);
   A.zp = static_cast<const T*>(c->zp.p);
   A.zs = static_cast<const T*>(c->zs.p);
-  // BF16x3 and FP64 at orders 5-7: one set for both kinds
+  // BF16x3 and FP64 at orders 5-7: one set
   A.frags = static_cast<const dgb::u32x4*>(one_element(c) && c->efrags.p ? c->efrags.p
                                                                          : c->frags.p);
   A.K = c->mesh.K;
@@ -407,13 +425,9 @@ hipError_t launch_mfma_e(dg_ctx* c, const float* q_in, float* q_out, float* res,
   A.dt = float(dt);
   A.lsrk = lsrk;
   if (c->mesh.K > 0x7fffffff) return hipErrorInvalidValue;
-  if (!one_element(c)) {
-    if constexpr (N >= 5)
-      return dgl::stage_bt<N, F32>(A, unsigned((c->mesh.K + dgb::kTile - 1) / dgb::kTile),
-                                   c->stream);
-    else
-      return hipErrorInvalidValue;   // orders 1-4: launch_mfma_n
-  }
+  if (!one_element(c))
+    return dgl::stage_bt<N, F32>(A, unsigned((c->mesh.K + dgb::kTile - 1) / dgb::kTile),
+                                 c->stream);
   // one workgroup per element
   return dgl::stage_be<N, F32>(A, unsigned(c->mesh.K), c->stream);
 }
@@ -443,19 +457,6 @@ dg_status launch_mfma(dg_ctx* c, const void* q_in, void* q_out, void* res, void*
   float* ro = static_cast<float*>(rhs_out);
   hipError_t e;
   const bool f32 = c->opt.precision == DG_FP32;
-  if (c->re.N <= 4 && one_element(c)) {
-    switch (c->re.N) {
-      case 2: e = f32 ? launch_mfma_e<2, true>(c, qi, qo, rs, ro, a, b, dt, lsrk)
-                      : launch_mfma_e<2, false>(c, qi, qo, rs, ro, a, b, dt, lsrk); break;
-      case 3: e = f32 ? launch_mfma_e<3, true>(c, qi, qo, rs, ro, a, b, dt, lsrk)
-                      : launch_mfma_e<3, false>(c, qi, qo, rs, ro, a, b, dt, lsrk); break;
-      default: e = f32 ? launch_mfma_e<4, true>(c, qi, qo, rs, ro, a, b, dt, lsrk)
-                       : launch_mfma_e<4, false>(c, qi, qo, rs, ro, a, b, dt, lsrk); break;
-    }
-    if (e != hipSuccess)
-      return fail(c, DG_EDEVICE, std::string("matrix-core stage launch: ") + hipGetErrorString(e));
-    return DG_OK;
-  }
   switch (c->re.N) {
     case 1: e = f32 ? launch_mfma_n<1, true>(c, qi, qo, rs, ro, a, b, dt, lsrk)
                     : launch_mfma_n<1, false>(c, qi, qo, rs, ro, a, b, dt, lsrk); break;
@@ -528,7 +529,7 @@ dg_status fill_zero(dg_ctx* c, void* p, int64_t n) {
 dg_status device_irho(dg_ctx* c, int64_t k, std::vector<double>& out) {
   const int Nq = c->re.Nq;
   out.assign(Nq, 0.0);
-  if (!plain_material(c->opt.precision, c->re.N, c->mesh.K)) {
+  if (!plain_material(c->opt.precision, c->re.N)) {
     for (int p = 0; p < Nq; ++p) {
       float v = 0.f;
       const size_t idx = dgh::mfma_material_index(c->re.N, k, p, 0);
@@ -1162,7 +1163,7 @@ dgb::BatchSlot batch_slot_of(const dg_ctx* c, double dt, int64_t first) {
   float* q0 = static_cast<float*>(c->q[c->cur].p);
   float* q1 = static_cast<float*>(c->q[1 - c->cur].p);
   float* res = static_cast<float*>(c->res.p);
-  if (c->re.N <= 4 && !one_element(c)) {
+  if (c->re.N <= 4) {
     dgb::BxArgs& A = S.k.bx;
     A.q_in = q0;
     A.q_out = q1;
@@ -1243,7 +1244,7 @@ dg_status batch_advance_impl(void* table, dgb::BatchSlot* slots, int max_slots, 
   if (s != DG_OK) return s;
   hipStream_t st = stream ? static_cast<hipStream_t>(stream) : c0->stream;
   // the slots of each stage kernel together (0: one element per workgroup, 1:
-  // tiles), with launch positions of their own
+  // tiles; both kinds at orders 5-7 only), with launch positions of their own
   int64_t pos[2] = {0, 0};
   int cnt[2] = {0, 0};
   bool any_src = false, any_rec = false;
@@ -1260,7 +1261,8 @@ dg_status batch_advance_impl(void* table, dgb::BatchSlot* slots, int max_slots, 
       max_np3 = std::max(max_np3, 3 * S.Np);
       max_rec3 = std::max(max_rec3, 3 * S.nrec);
     }
-  if (pos[0] > 0x7fffffff || pos[1] > 0x7fffffff) return fail(c0, DG_EINVAL, "batch: too many workgroups for one grid");
+  if (pos[0] > 0x7fffffff || pos[1] > 0x7fffffff)
+    return fail(c0, DG_EINVAL, "batch: too many workgroups for one grid");
   // the slot table, written by launches that carry it
   const size_t words = size_t(n) * sizeof(dgb::BatchSlot) / 4;
   static_assert(sizeof(dgb::BatchSlot) % 4 == 0, "whole words");
@@ -1367,30 +1369,28 @@ dg_status dg_create(dg_ctx** out, const dg_options* opt) {
         dg_destroy(c);
         return DG_ENOMEM;
       }
-      // orders 1-4 hold the fragments of both kinds (tens of KB)
-      const bool both = opt->order <= 4;
       if (opt->precision == DG_FP32_BF16X3) {
         const std::vector<uint16_t> fr = dgh::mfma_fragments(re);
-        const std::vector<uint16_t> fe = both ? dgh::element_fragments(re) : std::vector<uint16_t>();
-        if (upload_raw(c, c->frags, fr.data(), fr.size()) != DG_OK ||
-            (both && upload_raw(c, c->efrags, fe.data(), fe.size()) != DG_OK)) {
+        if (upload_raw(c, c->frags, fr.data(), fr.size()) != DG_OK) {
           dg_destroy(c);
           return DG_ENOMEM;
         }
       } else if (opt->precision == DG_FP32) {
         // tiles take FP32 fragments (orders 1, 2) or three bf16 parts (3-6), one
-        // element per workgroup FP32 fragments
-        const std::vector<float> fe = dgh::element_fragments_f32(re);
+        // element per workgroup (5-7) FP32 fragments
         const std::vector<float> ff =
             opt->order <= 2 ? dgh::mfma_fragments_f32(re) : std::vector<float>();
         const std::vector<uint16_t> f6 = dgh::mfma_fragments_bf16x6(re);
+        const std::vector<float> fe =
+            opt->order >= 5 ? dgh::element_fragments_f32(re) : std::vector<float>();
         if ((!ff.empty() && upload_raw(c, c->frags, ff.data(), ff.size()) != DG_OK) ||
-            upload_raw(c, c->efrags, fe.data(), fe.size()) != DG_OK ||
-            (!f6.empty() && upload_raw(c, c->frags, f6.data(), f6.size()) != DG_OK)) {
+            (!f6.empty() && upload_raw(c, c->frags, f6.data(), f6.size()) != DG_OK) ||
+            (!fe.empty() && upload_raw(c, c->efrags, fe.data(), fe.size()) != DG_OK)) {
           dg_destroy(c);
           return DG_ENOMEM;
         }
-      } else {   // FP64 on the matrix cores
+      } else {   // FP64 on the matrix cores: both kinds at orders 2-4 (tens of KB)
+        const bool both = opt->order >= 2 && opt->order <= 4;
         const std::vector<double> fr = dgh::mfma_fragments_f64(re);
         const std::vector<double> fe = both ? dgh::element_fragments_f64(re) : std::vector<double>();
         if (upload_raw(c, c->frags, fr.data(), fr.size()) != DG_OK ||
@@ -1567,7 +1567,7 @@ dg_status dg_material_upload(dg_ctx* c, const double* rho_q, const double* cp_q,
           dgh::mfma_material(c->re.N, K, a.data(), b.data(), d.data(), c->opt.precision == DG_FP64);
       if ((s = upload_real(c, c->matblk, blk.data(), blk.size())) != DG_OK) return s;
     }
-    if (plain_material(c->opt.precision, c->re.N, c->mesh.K)) {
+    if (plain_material(c->opt.precision, c->re.N)) {
       if ((s = upload_real(c, c->irho, a.data(), nq)) != DG_OK) return s;
       if ((s = upload_real(c, c->lam, b.data(), nq)) != DG_OK) return s;
       if ((s = upload_real(c, c->mu, d.data(), nq)) != DG_OK) return s;
@@ -2021,9 +2021,9 @@ dg_status dg_footprint(int32_t order, int32_t precision, int64_t K, int32_t nsrc
     else   // FP32: FP32 fragments (orders 1, 2) or three parts
       b += order <= 2 ? uint64_t(dgh::mfma_f64_frag_count(order)) * 16
                       : uint64_t(dgh::mfma_frag_count(order)) / 2 * 3 * 64 * 16;
-    if (order <= 4 || precision == DG_FP32)   // those of one element per workgroup
-      b += precision == DG_FP32_BF16X3 ? uint64_t(dgh::element_frag_count(order, true)) * 64 * 16
-         : uint64_t(dgh::element_frag_count(order, false)) * 64 * 4 * e;
+    // those of one element per workgroup (BF16x3 and FP64 at orders 5-7: above)
+    if (precision == DG_FP32 ? order >= 5 : precision == DG_FP64 && order >= 2 && order <= 4)
+      b += uint64_t(dgh::element_frag_count(order)) * 64 * 4 * e;
     b += k * (9 + 16) * e + k * 4 * 4 + k * 4 + 96 * Nfp * 4;          // geometry, tables
     b += 3 * 9 * k * Np * e + 2 * sizeof(double);                      // q[2], res, clock
     b += k * NF4 * 4;                                                   // neighbour nodes
@@ -2031,7 +2031,7 @@ dg_status dg_footprint(int32_t order, int32_t precision, int64_t K, int32_t nsrc
       b += ((k + 15) / 16) * 3 * uint64_t(dgh::mfma_mats(order)) * e;   // blocked material
       b += (k + 15) / 16 * 4;                                           // tile order
     }
-    if (plain_material(precision, order, K)) b += 3 * k * Nq * e;          // 1/rho, lam, mu
+    if (plain_material(precision, order)) b += 3 * k * Nq * e;          // 1/rho, lam, mu
     b += 2 * k * Np * e;                                                // impedances
     b += uint64_t(nsrc) * (8 + 3 * Np * e + 3 * 8);                     // sources
     b += uint64_t(nrec) * (8 + Np * e) + uint64_t(trace_steps) * nrec * 3 * e;   // receivers
@@ -2073,7 +2073,7 @@ dg_status dg_material_set_weights(dg_ctx* c, const double* irho_q, const double*
           dgh::mfma_material(c->re.N, K, irho_q, lam_q, mu_q, c->opt.precision == DG_FP64);
       if ((s = upload_real(c, c->matblk, blk.data(), blk.size())) != DG_OK) return s;
     }
-    if (plain_material(c->opt.precision, c->re.N, c->mesh.K)) {
+    if (plain_material(c->opt.precision, c->re.N)) {
       if ((s = upload_real(c, c->irho, irho_q, nq)) != DG_OK) return s;
       if ((s = upload_real(c, c->lam, lam_q, nq)) != DG_OK) return s;
       if ((s = upload_real(c, c->mu, mu_q, nq)) != DG_OK) return s;

@@ -1,7 +1,7 @@
 // Fused DG elastic-wave stage on the matrix cores (gfx950): one element per
-// workgroup, for contexts of few 16-element tiles at every order (their tiles
-// would leave most CUs idle) and where a tile does not fit in LDS (FP64 at
-// orders 5-7, FP32 at order 7).
+// workgroup, for contexts of few 16-element tiles at orders 5-7 and, in FP64, 2-4
+// (their tiles would leave most CUs idle), and where a tile needs more LDS than a
+// workgroup takes here (FP64 at orders 5-7, FP32 at order 7).
 //
 // The MFMA columns are the element's nine fields (and then its nine output
 // components) instead of sixteen elements; columns 9-15 carry zeros.  On a

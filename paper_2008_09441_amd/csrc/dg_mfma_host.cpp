@@ -252,7 +252,6 @@ std::vector<float> mfma_fragments_f32(const RefElement& re) {
 
 std::vector<uint16_t> element_fragments(const RefElement& re) {
   switch (re.N) {
-    case 1: return build_frags_e<1, 2>(re);
     case 2: return build_frags_e<2, 2>(re);
     case 3: return build_frags_e<3, 2>(re);
     case 4: return build_frags_e<4, 2>(re);
@@ -262,7 +261,6 @@ std::vector<uint16_t> element_fragments(const RefElement& re) {
 
 std::vector<float> element_fragments_f32(const RefElement& re) {
   switch (re.N) {
-    case 1: return build_frags_ef<1, float>(re);
     case 2: return build_frags_ef<2, float>(re);
     case 3: return build_frags_ef<3, float>(re);
     case 4: return build_frags_ef<4, float>(re);
@@ -274,7 +272,6 @@ std::vector<float> element_fragments_f32(const RefElement& re) {
 
 std::vector<double> element_fragments_f64(const RefElement& re) {
   switch (re.N) {
-    case 1: return build_frags_ef<1, double>(re);
     case 2: return build_frags_ef<2, double>(re);
     case 3: return build_frags_ef<3, double>(re);
     case 4: return build_frags_ef<4, double>(re);
@@ -398,15 +395,14 @@ std::vector<float> adj_fragments_f32(const RefElement& re) {
   }
 }
 
-int element_frag_count(int N, bool split) {
+int element_frag_count(int N) {
   switch (N) {
-    case 1: return split ? dgb::EOrd<1>::NFRAG : dgb::EFOrd<1>::NFRAG;
-    case 2: return split ? dgb::EOrd<2>::NFRAG : dgb::EFOrd<2>::NFRAG;
-    case 3: return split ? dgb::EOrd<3>::NFRAG : dgb::EFOrd<3>::NFRAG;
-    case 4: return split ? dgb::EOrd<4>::NFRAG : dgb::EFOrd<4>::NFRAG;
-    case 5: return split ? dgb::EOrd<5>::NFRAG : dgb::EFOrd<5>::NFRAG;
-    case 6: return split ? dgb::EOrd<6>::NFRAG : dgb::EFOrd<6>::NFRAG;
-    default: return split ? dgb::EOrd<7>::NFRAG : dgb::EFOrd<7>::NFRAG;
+    case 2: return dgb::EFOrd<2>::NFRAG;
+    case 3: return dgb::EFOrd<3>::NFRAG;
+    case 4: return dgb::EFOrd<4>::NFRAG;
+    case 5: return dgb::EFOrd<5>::NFRAG;
+    case 6: return dgb::EFOrd<6>::NFRAG;
+    default: return dgb::EFOrd<7>::NFRAG;
   }
 }
 

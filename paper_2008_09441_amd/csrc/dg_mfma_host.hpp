@@ -25,14 +25,15 @@ std::vector<uint16_t> mfma_fragments(const RefElement& re);
 std::vector<uint16_t> mfma_fragments_bf16x6(const RefElement& re);
 std::vector<float> mfma_fragments_f32(const RefElement& re);
 
-// fragments of the one-element-per-workgroup stage, which small meshes run at
-// every order: BF16x3 in the layout of EOrd, FP32 and FP64 in that of EFOrd
-// (at orders 5-7 BF16x3 and FP64 are those of mfma_fragments and _f64)
+// fragments of the one-element-per-workgroup stage, orders 2-7: BF16x3 in the
+// layout of EOrd, FP32 and FP64 in that of EFOrd (at orders 5-7 BF16x3 and FP64
+// are those of mfma_fragments and _f64).  Contexts take it at orders 5-7, in FP64
+// also at orders 2-4.
 std::vector<uint16_t> element_fragments(const RefElement& re);
 std::vector<float> element_fragments_f32(const RefElement& re);
 std::vector<double> element_fragments_f64(const RefElement& re);
-// their count at order N (of 64 lanes; split: hi and lo of EOrd, else EFOrd)
-int element_frag_count(int N, bool split);
+// fragments (of 64 lanes x 4 values) of the EFOrd layout at order N, 2-7
+int element_frag_count(int N);
 
 // FP64 operator fragments of the FP64 matrix-core stage: orders 1-4 in the
 // layout of FOrd ([NF4S][4] doubles), orders 5-7 in that of EFOrd

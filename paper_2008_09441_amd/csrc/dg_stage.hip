@@ -64,10 +64,11 @@ hipError_t stage_be_d(const dgb::BeArgsT<double>& A, unsigned grid, hipStream_t 
 template <int N, bool F32>
 hipError_t stage_batch(const dgb::BatchSlot* table, int n, unsigned grid, bool tiles,
                        hipStream_t st, int par, float a, float b) {
-  if (!tiles) {
-    dgb::stage_be_batch<N, F32><<<dim3(grid), dim3(dgb::kThreads), 0, st>>>(table, n, par, a, b);
-  } else if constexpr (N <= 4) {
+  if constexpr (N <= 4) {
+    if (!tiles) return hipErrorInvalidValue;
     dgb::stage_bx_batch<N, F32><<<dim3(grid), dim3(dgb::kThreads), 0, st>>>(table, n, par, a, b);
+  } else if (!tiles) {
+    dgb::stage_be_batch<N, F32><<<dim3(grid), dim3(dgb::kThreads), 0, st>>>(table, n, par, a, b);
   } else if constexpr (F32 && N > 6) {
     return hipErrorInvalidValue;
   } else {
@@ -84,10 +85,7 @@ hipError_t stage_batch(const dgb::BatchSlot* table, int n, unsigned grid, bool t
 #if DG_PART < 2
 DG_INST stage_batch<DG_ORDER, DG_PART == 1>(const dgb::BatchSlot*, int, unsigned, bool, hipStream_t,
                                             int, float, float);
-#endif
-#if DG_PART < 2
-DG_INST stage_be<DG_ORDER, DG_PART == 1>(const dgb::BeArgs&, unsigned, hipStream_t);
-#elif DG_PART == 2
+#elif DG_PART == 2 && DG_ORDER >= 2
 DG_INST stage_be_d<DG_ORDER>(const dgb::BeArgsT<double>&, unsigned, hipStream_t);
 #endif
 #if DG_ORDER <= 4
@@ -101,6 +99,7 @@ DG_INST stage_bx_r<DG_ORDER>(const dgb::BxArgs&, unsigned, hipStream_t);
 DG_INST adj_tile<DG_ORDER>(const dgt::TileArgs&, unsigned, hipStream_t);
 #endif
 #elif DG_PART < 2
+DG_INST stage_be<DG_ORDER, DG_PART == 1>(const dgb::BeArgs&, unsigned, hipStream_t);
 DG_INST stage_bt<DG_ORDER, DG_PART == 1>(const dgb::BeArgs&, unsigned, hipStream_t);
 #endif
 #undef DG_INST
