@@ -11,9 +11,12 @@
 //
 // Products are split products of P bf16 parts per operand, A B as the sum of
 // the leading part products with FP32 accumulation.  P = 2 (BF16x3: hi hi,
-// hi lo, lo hi) and P = 3 (three parts hold every bit of an FP32 value; of the
-// nine part products those below 2^-24 are left out: FP32, six products of 16
-// cycles per 32 K slots against eight of 32 for v_mfma_f32_16x16x4_f32).
+// hi lo, lo hi) and P = 3 (FP32: three parts hold every bit of an FP32 value; six
+// of the nine part products, see kProd in dg_bx.hpp, of 16 cycles each per 32 K
+// slots against eight of 32 for v_mfma_f32_16x16x4_f32).  With three parts,
+// elements of odd index carry the opposite sign from their fluxes and metric terms
+// to the result, so that what the products cut off downwards (kProd) does not add
+// up over the steps of a run.
 //
 // Measured against one element per workgroup (dg_be.hpp), us per stage on
 // 24,576 elements: BF16x3 order 5 307 -> 109, order 6 593 -> 292, order 7
@@ -531,7 +534,7 @@ __device__ __forceinline__ void stage_bt_run(const BeArgs& A, int64_t G, int64_t
         Q[f] = inT ? x : qP[it][f];
       }
       const float nx = fg[it][0], ny = fg[it][1], nz = fg[it][2];
-      const float fs = fg[it][3];
+      const float fs = P == 3 && idx / FK % 2 ? -fg[it][3] : fg[it][3];
       const float jtx = (Q[3] - M[3]) * nx + (Q[8] - M[8]) * ny + (Q[7] - M[7]) * nz;
       const float jty = (Q[8] - M[8]) * nx + (Q[4] - M[4]) * ny + (Q[6] - M[6]) * nz;
       const float jtz = (Q[7] - M[7]) * nx + (Q[6] - M[6]) * ny + (Q[5] - M[5]) * nz;
@@ -592,7 +595,10 @@ __device__ __forceinline__ void stage_bt_run(const BeArgs& A, int64_t G, int64_t
   if constexpr (!O::KEEPQ) load_q();   // again, from L2: registers
   float Ge[9];
 #pragma unroll
-  for (int i = 0; i < 9; ++i) Ge[i] = bt_ld<float>(A.geo + e0 * 9, 4u * unsigned(er * 9 + i));
+  for (int i = 0; i < 9; ++i) {
+    Ge[i] = bt_ld<float>(A.geo + e0 * 9, 4u * unsigned(er * 9 + i));
+    if (P == 3 && e % 2) Ge[i] = -Ge[i];
+  }
   bt_sync();
 
   const FragBuf F(A.frags, O::NFRAG, lane);
@@ -688,7 +694,7 @@ __device__ __forceinline__ void stage_bt_run(const BeArgs& A, int64_t G, int64_t
       if ((k == 2 && !three) || n0 >= Np || e >= ne) continue;
       const int64_t fb = t0 + bt_comp(O::G, grp, k) * KNp;
       const unsigned at = 4u * unsigned(e * Np + n0);
-      const f32x4 rr = fin[u][k];
+      const f32x4 rr = P == 3 && e % 2 ? -fin[u][k] : fin[u][k];
       if (A.lsrk) {
         const f32x4 rn = A.a * rv[u][k] + A.dt * rr;
         bt_stu(A.res + fb, at, rn);

@@ -142,8 +142,30 @@ __device__ __forceinline__ void split8(const float* v, bf16x8 (&o)[P]) {
 }
 
 // The part products of a split product A B: A part prod_a and B part prod_b of
-// product k < kProd<P>.  P = 2 (BF16x3): hi hi, hi lo, lo hi.  P = 3 (FP32): the
-// six whose order is not below 2^-24, from the smallest up.
+// product k < kProd<P>.  P = 2 (BF16x3): hi hi, hi lo, lo hi.  P = 3 (FP32): six
+// of nine, from the smallest up; a part is at most 2^-9 of the one before it, so
+// the three left out (second by third part, both ways, and third by third) are at
+// most 2^-27 of the product.
+//   What three parts have to mind: v_mfma_f32_16x16x32_bf16 adds four groups of
+// eight products to the accumulator in turn, and an accumulator smaller than the
+// largest product of a group is first cut off at that product's last FP32 bit,
+// downwards.  The error is small but has one sign, so that it adds up over the
+// steps of a run where rounding to nearest averages out (v_mfma_f32_16x16x4_f32
+// rounds to nearest).  Left alone, a right-hand side of order 4 is off by 1.8e-7
+// of its norm in the mean of 200 steps (5.9e-8 on FP32 products) and a state of
+// 3,072 elements by 3.2e-6 after 800 steps and 1.0e-5 after 3,200 (2.3e-6, 4.7e-6);
+// order 3 2.0e-6 and 5.3e-6 (1.8e-6, 3.9e-6).  Therefore:
+//   - an accumulator that holds whole products takes the leading product, and the
+//     five small ones have one of their own (mma_split);
+//   - every second K step is negated, and the accumulator with it, so that what is
+//     cut off cancels (the results then have the sign of the step count);
+//   - elements of odd index have the opposite sign from their fluxes and metric
+//     terms to the result, so that what is left cancels over neighbours;
+//   - the derivatives are taken of the state less its value at node mid_node, which
+//     they do not change: their products are large and nearly cancel.
+// 4.9e-8 so in the mean, and 2.3e-6 and 4.9e-6 (order 3 1.8e-6 and 3.7e-6); a stage
+// of 82,944 elements takes 125 us at order 3 and 288 at order 4 (124 and 282
+// without, 153 and 386 on FP32 products).
 template <int P>
 constexpr int kProd = P == 2 ? 3 : 6;
 __host__ __device__ constexpr int prod_a(int P, int k) {
@@ -152,22 +174,23 @@ __host__ __device__ constexpr int prod_a(int P, int k) {
 __host__ __device__ constexpr int prod_b(int P, int k) {
   return P == 2 ? (k == 1 ? 1 : 0) : (k == 1 ? 2 : k == 2 || k == 4 ? 1 : 0);
 }
-template <int P, bool APART = P == 3>
+// c + A B, with FLIP its negative (three parts)
+template <int P, bool FLIP = false>
 __device__ __forceinline__ f32x4 mma_split(const u32x4 (&a)[P], const bf16x8 (&b)[P], f32x4 c) {
-  if constexpr (!APART) {
+  if constexpr (P == 2) {
 #pragma unroll
     for (int k = 0; k < kProd<P>; ++k) c = mma(a[prod_a(P, k)], b[prod_b(P, k)], c);
     return c;
   } else {
-    // the small products on their own, so that c rounds at full size twice a step
-    // and not six times (an FP32 right-hand side of order 4 is 2.0e-6 off its
-    // FP64 value with six, less than the 1.7e-6 of FP32 products with two)
     f32x4 d = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int k = 0; k + 1 < kProd<P>; ++k) d = mma(a[prod_a(P, k)], b[prod_b(P, k)], d);
-    return mma(a[0], b[0], c) + d;
+    c = mma(a[0], b[0], c);
+    return FLIP ? -c - d : c + d;
   }
 }
+// a node near the element's centre: (1, 1, 1) of orders 3 on
+__host__ __device__ constexpr int mid_node(int N) { return (N + 1) * (N + 2) / 2 + N + 1; }
 
 // Uses accumulators where they are complete: products have no side effect, and
 // the compiler sinks those whose result is read in a later block into it, with
@@ -245,7 +268,10 @@ struct BLds {
   static constexpr int BYTES = USED > FLOOR ? USED : FLOOR;
 };
 
-// Phase C for wave W: acc[i][t] = rows 16 t + 4 g + j of r_{comp i}
+// Phase C for wave W: acc[i][t] = rows 16 t + 4 g + j of r_{comp i}, in three parts
+// negated where kNegC<N>
+template <int N>
+constexpr bool kNegC = (BOrd<N>::SVL - 1) & 1;
 template <int N, int W, int P>
 __device__ __forceinline__ void vol_lift(const BxArgs& A, const FragBuf& F, const float* sq, const float* sg,
                                          const float* sF, int lane, f32x4 (&acc)[3][BOrd<N>::RT]) {
@@ -260,6 +286,16 @@ __device__ __forceinline__ void vol_lift(const BxArgs& A, const FragBuf& F, cons
   for (int i = 0; i < NC; ++i)
 #pragma unroll
     for (int t = 0; t < RT; ++t) acc[i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  // three parts: the state at the middle node (see kProd)
+  float q0[NC][3];
+  if constexpr (P == 3) {
+#pragma unroll
+    for (int i = 0; i < NC; ++i)
+#pragma unroll
+      for (int j = 0; j < 3; ++j)
+        q0[i][j] = sq[(comp_field(wave_comp(W, i), j) * Np + mid_node(N)) * kES + e];
+  }
 
   // operator fragments are prefetched one K step ahead (the fragment reads
   // hit L2; without the prefetch each step waits for its own)
@@ -290,10 +326,14 @@ __device__ __forceinline__ void vol_lift(const BxArgs& A, const FragBuf& F, cons
           const int c = wave_comp(W, i);
           float a[3];
 #pragma unroll
-          for (int j = 0; j < 3; ++j)
-            a[j] = comp_weight(c, j) != 0.f
-                       ? comp_weight(c, j) * sq[(comp_field(c, j) * Np + m) * kES + e]
-                       : 0.f;
+          for (int j = 0; j < 3; ++j) {
+            a[j] = 0.f;
+            if (comp_weight(c, j) != 0.f) {
+              a[j] = sq[(comp_field(c, j) * Np + m) * kES + e];
+              if constexpr (P == 3) a[j] -= q0[i][j];
+              a[j] *= comp_weight(c, j);
+            }
+          }
 #pragma unroll
           for (int d = 0; d < 3; ++d) {
             float u = 0.f;
@@ -320,11 +360,19 @@ __device__ __forceinline__ void vol_lift(const BxArgs& A, const FragBuf& F, cons
     }
     bf16x8 b[NC][P];
 #pragma unroll
-    for (int i = 0; i < NC; ++i) split8<P>(bv[i], b[i]);
+    for (int i = 0; i < NC; ++i) {
+      if (P == 3 && s % 2) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) bv[i][j] = -bv[i][j];
+      }
+      split8<P>(bv[i], b[i]);
+    }
 #pragma unroll
     for (int t = 0; t < RT; ++t) {
 #pragma unroll
-      for (int i = 0; i < NC; ++i) acc[i][t] = mma_split<P>(fc[t], b[i], acc[i][t]);
+      for (int i = 0; i < NC; ++i)
+        acc[i][t] = s + 1 < SVL ? mma_split<P, P == 3>(fc[t], b[i], acc[i][t])
+                                : mma_split<P>(fc[t], b[i], acc[i][t]);
       if (P == 3) __builtin_amdgcn_sched_barrier(0);   // registers
     }
 #pragma unroll
@@ -462,14 +510,19 @@ __device__ __forceinline__ void quad_proj(const BxArgs& A, const FragBuf& F, int
           }
           if (PK == 3) __builtin_amdgcn_sched_barrier(0);   // parked parts one step at a time
         }
-        if constexpr (P == 3) {   // the leading products after the small ones of every step
+        if constexpr (P == 3) {   // the leading products on their own
+          f32x4 wl[NC];
+#pragma unroll
+          for (int i = 0; i < NC; ++i) wl[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
           for (int s = 0; s < SVQ; ++s)
 #pragma unroll
             for (int i = 0; i < NC; ++i) {
               if (PK > 0) r[i][s][0] = *pk(i, s, 0);
-              w[i][u] = mma(fv[u][s][0], r[i][s][0], w[i][u]);
+              wl[i] = mma(fv[u][s][0], r[i][s][0], wl[i]);
             }
+#pragma unroll
+          for (int i = 0; i < NC; ++i) w[i][u] += wl[i];
         }
       }
       if (P == 3) __builtin_amdgcn_sched_barrier(0);
@@ -507,18 +560,22 @@ __device__ __forceinline__ void quad_proj(const BxArgs& A, const FragBuf& F, int
     for (int i = 0; i < NC; ++i) {
       float v[8];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) v[j] = w[i][j / 4][j % 4];
+      for (int j = 0; j < 8; ++j) v[j] = P == 3 && ch % 2 ? -w[i][j / 4][j % 4] : w[i][j / 4][j % 4];
       split8<P>(v, p[i]);
     }
 #pragma unroll
     for (int t = 0; t < RT; ++t)
 #pragma unroll
-      for (int i = 0; i < NC; ++i) out[i][t] = mma_split<P, false>(fp[t], p[i], out[i][t]);
+      for (int i = 0; i < NC; ++i)
+        out[i][t] = ch + 1 < QC ? mma_split<P, P == 3>(fp[t], p[i], out[i][t])
+                                : mma_split<P>(fp[t], p[i], out[i][t]);
     if (P == 2 && ch + 1 < QC) {
 #pragma unroll
       for (int f = 0; f < 3; ++f) m[f][0] = mn[f][0], m[f][1] = mn[f][1];
     }
   }
+  // the signs of both phases and of odd elements
+  const bool neg = P == 3 && (kNegC<N> + QC - 1 + e) % 2;
 #pragma unroll
   for (int i = 0; i < NC; ++i)
 #pragma unroll
@@ -526,7 +583,7 @@ __device__ __forceinline__ void quad_proj(const BxArgs& A, const FragBuf& F, int
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int n = 16 * t + 4 * g + j;
-        if (n < Np) sr[(wave_comp(W, i) * Np + n) * kES + e] = out[i][t][j];
+        if (n < Np) sr[(wave_comp(W, i) * Np + n) * kES + e] = neg ? -out[i][t][j] : out[i][t][j];
       }
 }
 
@@ -774,6 +831,9 @@ __device__ __forceinline__ void stage_bx_run(const BxArgsT<T>& A, int64_t G, int
   using L = BLds<N, T>;
   using V4 = v4_t<T>;
   constexpr int Np = O::Np, Nfp = O::Nfp, NF4 = O::NF4, RT = O::RT;
+  constexpr bool plain = sizeof(T) == 8 || FP || (F32 && !bx_three_parts(N));   // FOrd fragments
+  constexpr int NP = F32 ? 3 : 2;                   // else split products of NP bf16 parts
+  constexpr bool alternate = !plain && NP == 3;     // odd elements negated (see kProd)
   __shared__ __align__(16) T smem[L::BYTES / sizeof(T)];
   T* sq = smem;                   // [9][Np][17]
   T* sg = sq + L::SQ;             // [16][9]
@@ -854,7 +914,8 @@ __device__ __forceinline__ void stage_bx_run(const BxArgsT<T>& A, int64_t G, int
       for (int f = 0; f < 9; ++f) vm[it][f] = (qt + f * KNp)[tm.main_row(tid, it)];
 #pragma unroll
     for (int j = 0; j < TileMap<N>::IT; ++j) vt[j] = qt[tm.tail_field(tid, j) * KNp + tm.tail_row(tid, j)];
-    const T gv = tid < kTile * 9 && tid / 9 < ne ? A.geo[e0 * 9 + tid] : T(0);
+    T gv = tid < kTile * 9 && tid / 9 < ne ? A.geo[e0 * 9 + tid] : T(0);
+    if (alternate && tid / 9 % 2) gv = -gv;
     constexpr int IZ = (kTile * Np + kThreads - 1) / kThreads;
     T zv[2][IZ];
 #pragma unroll
@@ -961,7 +1022,8 @@ __device__ __forceinline__ void stage_bx_run(const BxArgsT<T>& A, int64_t G, int
         dvx = T(0.5) * jvx; dvy = T(0.5) * jvy; dvz = T(0.5) * jvz;
         dtx = T(0.5) * jtx; dty = T(0.5) * jty; dtz = T(0.5) * jtz;
       }
-      const T z = ok[it] ? fs : T(0);   // zero flux outside the tile
+      T z = ok[it] ? fs : T(0);   // zero flux outside the tile
+      if (alternate && e % 2) z = -z;
       T fl[9];
       fl[0] = z * dtx;
       fl[1] = z * dty;
@@ -984,17 +1046,15 @@ __device__ __forceinline__ void stage_bx_run(const BxArgsT<T>& A, int64_t G, int
   // FP32 products, FP64 on the FP64 products)
   V4 acc[3][RT];
   V4 m0[3][2];   // chunk-0 material, in flight during phase C
-  constexpr int P = F32 ? 3 : 2;
-  constexpr bool plain = sizeof(T) == 8 || FP || (F32 && !bx_three_parts(N));   // FOrd fragments
-  const FragBuf F(A.frags, O::NFRAG * P, lane);   // split products
+  const FragBuf F(A.frags, O::NFRAG * NP, lane);   // split products
   const FragBufF<T> FF(A.frags, FOrd<N>::NF4S, lane);
   auto phase_c = [&](auto w) {
     constexpr int W = decltype(w)::value;
     // FP32: after the products (registers)
-    constexpr bool late = P == 3 && !plain;
+    constexpr bool late = NP == 3 && !plain;
     if constexpr (!late) mat_chunk<N, W, T>(A, tile, lane, 0, m0);
     if constexpr (plain) vol_lift_f<N, W, T>(FF, sq, sg, sF, lane, acc);
-    else vol_lift<N, W, P>(A, F, sq, sg, sF, lane, acc);
+    else vol_lift<N, W, NP>(A, F, sq, sg, sF, lane, acc);
     if constexpr (late) mat_chunk<N, W, T>(A, tile, lane, 0, m0);
     if constexpr (RST) store_raw<N, W>(A, e0, ne, lane, acc);
   };
@@ -1010,7 +1070,7 @@ __device__ __forceinline__ void stage_bx_run(const BxArgsT<T>& A, int64_t G, int
   auto phase_d = [&](auto w) {
     constexpr int W = decltype(w)::value;
     if constexpr (plain) quad_proj_f<N, W, T>(A, FF, tile, lane, acc, m0, sr);
-    else quad_proj<N, W, P>(A, F, tile, lane, acc, m0, sr, srl, srl2);
+    else quad_proj<N, W, NP>(A, F, tile, lane, acc, m0, sr, srl, srl2);
   };
   switch (grp) {
     case 0: phase_d(std::integral_constant<int, 0>()); break;
