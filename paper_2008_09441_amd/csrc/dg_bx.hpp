@@ -207,39 +207,57 @@ __device__ __forceinline__ void mma_done(f32x4 (&v)[M]) {
 // fragment offset and the lane's slot, so that one register addresses them all
 // (BF16x3, order 4: 233 registers and 1685 us at 663,552 elements, against 247
 // and 1714 with a 64-bit address per fragment row)
-struct FragBuf {
+template <typename V>
+struct FragBufV {
   __amdgpu_buffer_rsrc_t r;
   int lane16;
-  __device__ FragBuf(const void* frags, int count, int lane)
+  __device__ FragBufV(const void* frags, int count, int lane)
       : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(frags), 0, count * 1024, 0x00020000)),
         lane16(lane * 16) {}
-  __device__ __forceinline__ u32x4 load(int f) const {
-    return __builtin_amdgcn_raw_buffer_load_b128(r, lane16, f * 1024, 0);
+  __device__ __forceinline__ V load(int f, int i = 0) const {
+    return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(r, lane16, (f + i) * 1024, 0));
   }
 };
+using FragBuf = FragBufV<u32x4>;
 
-// the same for the four-value fragments of FOrd (64 lanes x 4 values each).  With
-// 64-bit addresses the FP64 stage takes 876 us at order 4 and 384 at order 3
-// (82,944 elements), with these 848 and 377; FP32 at orders 1 and 2 is unchanged.
-template <typename T>
-struct FragBufF {
+// the same for the four-value fragments of FOrd in FP64 (64 lanes x 4 doubles).
+// With 64-bit addresses the FP64 stage takes 876 us at order 4 and 384 at order 3
+// (82,944 elements), with these 848 and 377.
+struct FragBufD {
   __amdgpu_buffer_rsrc_t r;
   int off;
-  __device__ FragBufF(const void* frags, int count, int lane)
-      : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(frags), 0, count * int(4 * sizeof(T)),
-                                            0x00020000)),
-        off(lane * int(4 * sizeof(T))) {}
-  __device__ __forceinline__ v4_t<T> load(int f) const {
+  __device__ FragBufD(const void* frags, int count, int lane)
+      : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(frags), 0, count * 2048, 0x00020000)),
+        off(lane * 32) {}
+  __device__ __forceinline__ f64x4 load(int f, int k = 0) const {
     union {
-      u32x4 u[sizeof(T) / 4];
-      v4_t<T> v;
+      u32x4 u[2];
+      f64x4 v;
     } x;
 #pragma unroll
-    for (int i = 0; i < int(sizeof(T)) / 4; ++i)
-      x.u[i] = __builtin_amdgcn_raw_buffer_load_b128(r, off + 16 * i, f * int(256 * sizeof(T)), 0);
+    for (int i = 0; i < 2; ++i)
+      x.u[i] = __builtin_amdgcn_raw_buffer_load_b128(r, off + 16 * i, (f + k) * 2048, 0);
     return x.v;
   }
 };
+
+// fragments of 64 lanes x V by address: FP32 and BF16x3 at orders 1 and 2, whose
+// few fragments take more registers with a descriptor than they save (order 2, FP32,
+// 3,075 elements: 7.86 us a stage so, 7.93 with one)
+template <typename V>
+struct FragPtr {
+  const V* p;
+  int lane;
+  __device__ FragPtr(const void* frags, int, int l) : p(static_cast<const V*>(frags)), lane(l) {}
+  __device__ __forceinline__ V load(int f, int i = 0) const { return (p + f * 64)[i * 64 + lane]; }
+};
+
+// the form at order N of split products, and of FOrd fragments
+template <int N>
+using FragsS = std::conditional_t<(N <= 2), FragPtr<u32x4>, FragBuf>;
+template <int N, typename T>
+using FragsF = std::conditional_t<sizeof(T) == 8, FragBufD,
+                                  std::conditional_t<(N <= 2), FragPtr<f32x4>, FragBufV<f32x4>>>;
 
 // LDS use of one workgroup, in values of T, and its padded allocation in bytes
 template <int N, typename T = float>
@@ -273,7 +291,7 @@ struct BLds {
 template <int N>
 constexpr bool kNegC = (BOrd<N>::SVL - 1) & 1;
 template <int N, int W, int P>
-__device__ __forceinline__ void vol_lift(const BxArgs& A, const FragBuf& F, const float* sq, const float* sg,
+__device__ __forceinline__ void vol_lift(const BxArgs& A, const FragsS<N>& F, const float* sq, const float* sg,
                                          const float* sF, int lane, f32x4 (&acc)[3][BOrd<N>::RT]) {
   using O = BOrd<N>;
   constexpr int Np = O::Np, NF4 = O::NF4, RT = O::RT, SN = O::SN, SVL = O::SVL;
@@ -405,7 +423,7 @@ __device__ __forceinline__ void mat_chunk(const BxArgsT<T>& A, int64_t tile, int
 // Phase D for wave W: V_q, material, P_q; the nodal result goes to sr.  m0
 // holds the material of chunk 0 (loaded before phase C).
 template <int N, int W, int P>
-__device__ __forceinline__ void quad_proj(const BxArgs& A, const FragBuf& F, int64_t tile, int lane,
+__device__ __forceinline__ void quad_proj(const BxArgs& A, const FragsS<N>& F, int64_t tile, int lane,
                                           const f32x4 (&acc)[3][BOrd<N>::RT],
                                           const f32x4 (&m0)[3][2], float* sr, bf16x8* srl,
                                           bf16x8* srl2) {
@@ -602,7 +620,7 @@ __device__ __forceinline__ double rcp_t(double x) { return 1.0 / x; }
 // 16 t + 4 g + j of r_{comp i}, one K slot per lane and step (the order of
 // FOrd); operator fragments are fetched one group of four steps ahead.
 template <int N, int W, typename T>
-__device__ __forceinline__ void vol_lift_f(const FragBufF<T>& F, const T* sq, const T* sg,
+__device__ __forceinline__ void vol_lift_f(const FragsF<N, T>& F, const T* sq, const T* sg,
                                            const T* sF, int lane,
                                            v4_t<T> (&acc)[3][BOrd<N>::RT]) {
   using O = FOrd<N>;
@@ -619,12 +637,12 @@ __device__ __forceinline__ void vol_lift_f(const FragBufF<T>& F, const T* sq, co
     for (int t = 0; t < RT; ++t) acc[i][t] = V4{0, 0, 0, 0};
   V4 fc[RT], fn[RT];
 #pragma unroll
-  for (int t = 0; t < RT; ++t) fc[t] = F.load(O::OFF_V / 64 + t * SV4);
+  for (int t = 0; t < RT; ++t) fc[t] = F.load(O::OFF_V / 64, t * SV4);
 #pragma unroll
   for (int q = 0; q < SV4; ++q) {
     if (q + 1 < SV4) {
 #pragma unroll
-      for (int t = 0; t < RT; ++t) fn[t] = F.load(O::OFF_V / 64 + t * SV4 + q + 1);
+      for (int t = 0; t < RT; ++t) fn[t] = F.load(O::OFF_V / 64, t * SV4 + q + 1);
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -689,7 +707,7 @@ __device__ __forceinline__ void store_raw(const BxArgs& A, int64_t e0, int ne, i
 // P_q with the weighted values as the B operand (K step (u, j) is point
 // 16 u + 4 g + j); the nodal result goes to sr.
 template <int N, int W, typename T>
-__device__ __forceinline__ void quad_proj_f(const BxArgsT<T>& A, const FragBufF<T>& F, int64_t tile, int lane,
+__device__ __forceinline__ void quad_proj_f(const BxArgsT<T>& A, const FragsF<N, T>& F, int64_t tile, int lane,
                                             const v4_t<T> (&acc)[3][BOrd<N>::RT],
                                             const v4_t<T> (&m0)[3][2], T* sr) {
   using O = FOrd<N>;
@@ -713,8 +731,8 @@ __device__ __forceinline__ void quad_proj_f(const BxArgsT<T>& A, const FragBufF<
       const int qt = 2 * ch + u < QT ? 2 * ch + u : QT - 1;
 #pragma unroll
       for (int t = 0; t < RT; ++t) {
-        fv[u][t] = F.load(O::OFF_Q / 64 + qt * RT + t);
-        fp[t][u] = F.load(O::OFF_P / 64 + t * QT + qt);
+        fv[u][t] = F.load(O::OFF_Q / 64, qt * RT + t);
+        fp[t][u] = F.load(O::OFF_P / 64, t * QT + qt);
       }
     }
     V4 mn[3][2];
@@ -819,6 +837,17 @@ struct TileMap {
 // cost more than the FP32 products they replace (3,072 elements: order 1 5.0 us
 // against 5.8, order 2 7.8 against 8.3)
 constexpr bool bx_three_parts(int N) { return N >= 3; }
+
+// Phase C of wave W on split products, with the material of chunk 0 loaded before
+// the products, or after them (LATE)
+template <int N, int W, int P, bool LATE>
+__device__ __forceinline__ void split_c(const BxArgs& A, const FragsS<N>& F, int64_t tile,
+                                        const float* sq, const float* sg, const float* sF, int lane,
+                                        f32x4 (&m0)[3][2], f32x4 (&acc)[3][BOrd<N>::RT]) {
+  if constexpr (!LATE) mat_chunk<N, W>(A, tile, lane, 0, m0);
+  vol_lift<N, W, P>(A, F, sq, sg, sF, lane, acc);
+  if constexpr (LATE) mat_chunk<N, W>(A, tile, lane, 0, m0);
+}
 
 // The stage of one tile: launch position bid of a grid of G positions over
 // the context's tiles (G = ceil(K / 16)); the kernels below call it for a
@@ -1046,37 +1075,49 @@ __device__ __forceinline__ void stage_bx_run(const BxArgsT<T>& A, int64_t G, int
   // FP32 products, FP64 on the FP64 products)
   V4 acc[3][RT];
   V4 m0[3][2];   // chunk-0 material, in flight during phase C
-  const FragBuf F(A.frags, O::NFRAG * NP, lane);   // split products
-  const FragBufF<T> FF(A.frags, FOrd<N>::NF4S, lane);
-  auto phase_c = [&](auto w) {
-    constexpr int W = decltype(w)::value;
-    // FP32: after the products (registers)
-    constexpr bool late = NP == 3 && !plain;
-    if constexpr (!late) mat_chunk<N, W, T>(A, tile, lane, 0, m0);
-    if constexpr (plain) vol_lift_f<N, W, T>(FF, sq, sg, sF, lane, acc);
-    else vol_lift<N, W, NP>(A, F, sq, sg, sF, lane, acc);
-    if constexpr (late) mat_chunk<N, W, T>(A, tile, lane, 0, m0);
-    if constexpr (RST) store_raw<N, W>(A, e0, ne, lane, acc);
-  };
-  switch (grp) {
-    case 0: phase_c(std::integral_constant<int, 0>()); break;
-    case 1: phase_c(std::integral_constant<int, 1>()); break;
-    case 2: phase_c(std::integral_constant<int, 2>()); break;
-    default: phase_c(std::integral_constant<int, 3>()); break;
+  const FragsS<N> F(A.frags, O::NFRAG * NP, lane);   // split products
+  const FragsF<N, T> FF(A.frags, FOrd<N>::NF4S / 64, lane);
+  if constexpr (plain) {
+    switch (grp) {
+      case 0: mat_chunk<N, 0, T>(A, tile, lane, 0, m0); vol_lift_f<N, 0, T>(FF, sq, sg, sF, lane, acc); break;
+      case 1: mat_chunk<N, 1, T>(A, tile, lane, 0, m0); vol_lift_f<N, 1, T>(FF, sq, sg, sF, lane, acc); break;
+      case 2: mat_chunk<N, 2, T>(A, tile, lane, 0, m0); vol_lift_f<N, 2, T>(FF, sq, sg, sF, lane, acc); break;
+      default: mat_chunk<N, 3, T>(A, tile, lane, 0, m0); vol_lift_f<N, 3, T>(FF, sq, sg, sF, lane, acc); break;
+    }
+    if constexpr (RST) {
+      switch (grp) {
+        case 0: store_raw<N, 0>(A, e0, ne, lane, acc); break;
+        case 1: store_raw<N, 1>(A, e0, ne, lane, acc); break;
+        case 2: store_raw<N, 2>(A, e0, ne, lane, acc); break;
+        default: store_raw<N, 3>(A, e0, ne, lane, acc); break;
+      }
+    }
+  } else {
+    constexpr bool late = NP == 3;   // the material after the products (registers)
+    switch (grp) {
+      case 0: split_c<N, 0, NP, late>(A, F, tile, sq, sg, sF, lane, m0, acc); break;
+      case 1: split_c<N, 1, NP, late>(A, F, tile, sq, sg, sF, lane, m0, acc); break;
+      case 2: split_c<N, 2, NP, late>(A, F, tile, sq, sg, sF, lane, m0, acc); break;
+      default: split_c<N, 3, NP, late>(A, F, tile, sq, sg, sF, lane, m0, acc); break;
+    }
   }
   __syncthreads();   // fluxes consumed: sr may overwrite them
 
   // D: quadrature and projection per wave
-  auto phase_d = [&](auto w) {
-    constexpr int W = decltype(w)::value;
-    if constexpr (plain) quad_proj_f<N, W, T>(A, FF, tile, lane, acc, m0, sr);
-    else quad_proj<N, W, NP>(A, F, tile, lane, acc, m0, sr, srl, srl2);
-  };
-  switch (grp) {
-    case 0: phase_d(std::integral_constant<int, 0>()); break;
-    case 1: phase_d(std::integral_constant<int, 1>()); break;
-    case 2: phase_d(std::integral_constant<int, 2>()); break;
-    default: phase_d(std::integral_constant<int, 3>()); break;
+  if constexpr (plain) {
+    switch (grp) {
+      case 0: quad_proj_f<N, 0, T>(A, FF, tile, lane, acc, m0, sr); break;
+      case 1: quad_proj_f<N, 1, T>(A, FF, tile, lane, acc, m0, sr); break;
+      case 2: quad_proj_f<N, 2, T>(A, FF, tile, lane, acc, m0, sr); break;
+      default: quad_proj_f<N, 3, T>(A, FF, tile, lane, acc, m0, sr); break;
+    }
+  } else {
+    switch (grp) {
+      case 0: quad_proj<N, 0, NP>(A, F, tile, lane, acc, m0, sr, srl, srl2); break;
+      case 1: quad_proj<N, 1, NP>(A, F, tile, lane, acc, m0, sr, srl, srl2); break;
+      case 2: quad_proj<N, 2, NP>(A, F, tile, lane, acc, m0, sr, srl, srl2); break;
+      default: quad_proj<N, 3, NP>(A, F, tile, lane, acc, m0, sr, srl, srl2); break;
+    }
   }
 
   // E: right-hand side store or fused stage update, coalesced, done by the
