@@ -2018,7 +2018,7 @@ dg_status dg_footprint(int32_t order, int32_t precision, int64_t K, int32_t nsrc
     b += NF4 * 4;                                                       // face masks
     if (precision == DG_FP32_BF16X3) b += uint64_t(dgh::mfma_frag_count(order)) * 64 * 8 * 2;
     else if (precision == DG_FP64) b += uint64_t(dgh::mfma_f64_frag_count(order)) * 32;
-    else   // FP32: FP32 fragments (orders 1, 2) or three parts
+    else if (order <= 6)   // FP32 tiles: FP32 fragments (orders 1, 2) or three parts
       b += order <= 2 ? uint64_t(dgh::mfma_f64_frag_count(order)) * 16
                       : uint64_t(dgh::mfma_frag_count(order)) / 2 * 3 * 64 * 16;
     // those of one element per workgroup (BF16x3 and FP64 at orders 5-7: above)
