@@ -280,8 +280,8 @@ dg_status dg_material_set_weights(dg_ctx* ctx, const double* irho_q, const doubl
  * the receiver velocities after every step to trace (host
  * [nsteps][nrec][3], working precision).  Leaves the context at the end of
  * the run.  Needs receivers (DG_ESTATE).  Library-owned device memory:
- * ceil(nsteps/every) + 5 every + 6 states (FP32 at orders 1-4: 10 every + 6,
- * the replay also keeping R y of every stage input, or 20 every + 6 when
+ * ceil(nsteps/every) + 5 every + 5 states (FP32 at orders 1-4: 10 every + 5,
+ * the replay also keeping R y of every stage input, or 20 every + 5 when
  * that much fits, so that the replay of the next interval overlaps the
  * reverse sweep of this one) plus face-node work arrays
  * ([K][4 Nfp][9], two of them on the generic adjoint kernels) and the FP64

@@ -111,7 +111,8 @@ struct dg_ctx {
   DevBuf adj_nbface, adj_invf;
   DevBuf adj_ck;            // checkpoints [nck][9][K][Np]
   DevBuf adj_seg;           // stage inputs of one segment [every][5][9][K][Np]
-  DevBuf adj_v;             // ly, lres, mu, r, res [5][9][K][Np] (tiled: six, see there)
+  DevBuf adj_v;             // ly, lres, mu, r, res (tiled: ly, lres, res2, nu, res)
+                            // [5][9][K][Np]
   DevBuf adj_gb, adj_hb;    // face-node work [K][4 Nfp][9]
   DevBuf adj_grad;          // double [3][K][Nq]
   DevBuf adj_zb;            // upwind: impedance terms per face node [K][4 Nfp][4]
@@ -879,7 +880,7 @@ dg_status adj_backward_tiled(dg_ctx* c, const float* resid) {
   float* v = static_cast<float*>(c->adj_v.p);
   // res and res2 (a scratch output for a segment's last stage) are the
   // replay's; ly, lres and nu the reverse sweep's
-  float *ly = v, *lres = v + n, *res2 = v + 2 * n, *nu = v + 3 * n, *res = v + 5 * n;
+  float *ly = v, *lres = v + n, *res2 = v + 2 * n, *nu = v + 3 * n, *res = v + 4 * n;
   double* grad = static_cast<double*>(c->adj_grad.p);
   double* gradz = static_cast<double*>(c->adj_gradz.p);
   const double t0 = c->adj_t0, dt = c->adj_dt;
@@ -2138,7 +2139,7 @@ dg_status dg_adjoint_forward(dg_ctx* c, double t0, double dt, int64_t nsteps, in
     } need[] = {{&c->adj_ck, S * nck},
                 {&c->adj_seg, segb * nseg},
                 {&c->adj_r, tiled ? segb * nseg : 0},
-                {&c->adj_v, S * (tiled ? 6 : 5)},
+                {&c->adj_v, S * 5},
                 {&c->adj_gb, size_t(K) * NF4 * 9 * c->elem},
                 {&c->adj_hb, tiled ? 0 : size_t(K) * NF4 * 9 * c->elem},
                 {&c->adj_grad, size_t(K) * Nq * 3 * sizeof(double)},
