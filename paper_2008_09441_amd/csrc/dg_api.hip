@@ -119,7 +119,7 @@ struct dg_ctx {
                             // (tiled adjoint: face-node jumps [K][4 Nfp][8])
   DevBuf adj_gradz;         // upwind: double [2][K][Np]
   DevBuf adj_frag;          // FP32 orders 1-4: fragments of the tiled adjoint kernel
-  DevBuf adj_ffrag;         // and those of its FP32-product stages
+  DevBuf adj_ffrag;         // FP32 orders 3, 4: those of the adjoint's FP32-product stages
   DevBuf adj_r;             // FP32 orders 1-4: R y of every stage input of a segment,
                             // [every][5][9][K][Np] (stored by the replay)
   bool adj_ov = false;      // adj_seg and adj_r hold two segments: the replay of
@@ -374,7 +374,8 @@ dg_status launch_stage(dg_ctx* c, const void* q_in, void* q_out, void* res, void
   return DG_OK;
 }
 
-// RST, FP: the adjoint's stages on FP32 products (stage_bx_r, stage_bx_p)
+// RST, FP: the adjoint's stages on FP32 products (stage_bx_r, stage_bx_p), whose
+// fragments are the context's own at orders 1 and 2
 template <int N, bool F32, bool RST = false, bool FP = false>
 hipError_t launch_mfma_n(dg_ctx* c, const float* q_in, float* q_out, float* res, float* rhs_out,
                          double a, double b, double dt, int lsrk, float* r_out = nullptr,
@@ -404,7 +405,7 @@ hipError_t launch_mfma_n(dg_ctx* c, const float* q_in, float* q_out, float* res,
   if (tiles > 0x7fffffff) return hipErrorInvalidValue;
   A.r_out = r_out;
   A.j_out = j_out;
-  if constexpr (RST || FP) A.frags = static_cast<const dgb::u32x4*>(c->adj_ffrag.p);
+  if constexpr (N >= 3 && (RST || FP)) A.frags = static_cast<const dgb::u32x4*>(c->adj_ffrag.p);
   if constexpr (RST)
     return dgl::stage_bx_r<N>(A, unsigned(tiles), c->stream);
   else if constexpr (FP)
@@ -493,8 +494,8 @@ dg_status adj_stage(dg_ctx* c, const void* q_in, void* q_out, void* res, double 
   float* rs = static_cast<float*>(res);
   hipError_t e;
   switch (c->re.N) {
-    case 1: e = launch_mfma_n<1, true, false, true>(c, qi, qo, rs, nullptr, a, b, dt, 1); break;
-    case 2: e = launch_mfma_n<2, true, false, true>(c, qi, qo, rs, nullptr, a, b, dt, 1); break;
+    case 1: e = launch_mfma_n<1, true>(c, qi, qo, rs, nullptr, a, b, dt, 1); break;
+    case 2: e = launch_mfma_n<2, true>(c, qi, qo, rs, nullptr, a, b, dt, 1); break;
     case 3: e = launch_mfma_n<3, true, false, true>(c, qi, qo, rs, nullptr, a, b, dt, 1); break;
     case 4: e = launch_mfma_n<4, true, false, true>(c, qi, qo, rs, nullptr, a, b, dt, 1); break;
     case 5: e = launch_element_f32<5>(c, qi, qo, rs, a, b, dt); break;
@@ -765,8 +766,10 @@ dg_status adj_tables(dg_ctx* c) {
   if (adj_tiled(c)) {
     const std::vector<float> fr = dgh::adj_fragments_f32(re);
     if ((st = upload_raw(c, c->adj_frag, fr.data(), fr.size())) != DG_OK) return st;
-    const std::vector<float> ff = dgh::mfma_fragments_f32(re);
-    if ((st = upload_raw(c, c->adj_ffrag, ff.data(), ff.size())) != DG_OK) return st;
+    if (re.N >= 3) {
+      const std::vector<float> ff = dgh::mfma_fragments_f32(re);
+      if ((st = upload_raw(c, c->adj_ffrag, ff.data(), ff.size())) != DG_OK) return st;
+    }
   }
   if ((st = upload_raw(c, c->adj_nbface, nbf.data(), nbf.size())) != DG_OK) return st;
   return upload_raw(c, c->adj_invf, invf.data(), invf.size());
@@ -1022,7 +1025,9 @@ dg_status adj_backward_t(dg_ctx* c, const T* resid) {
   // per-element kernels: one workgroup per element, the element's vectors in LDS
   if (K > 0x7fffffff) return fail(c, DG_EINVAL, "adjoint: too many elements for one grid");
   const dim3 eg(static_cast<unsigned>(K)), et(static_cast<unsigned>(dga::kAdjThreads));
-  const bool split = dga::adj_split(Np);
+  // FP32 elements this small take the tiled adjoint
+  constexpr bool f64 = sizeof(T) == 8;
+  const bool split = f64 && dga::adj_split(Np);
   const dim3 traw(dga::adj_threads(dga::raw_s_items(Np, c->re.Nfp)));
   const dim3 tgw(dga::adj_threads(3 * Nq));
   const size_t lraw = size_t(split ? dga::raw_s_lds_elems(Np, c->re.Nfp)
@@ -1077,8 +1082,9 @@ dg_status adj_backward_t(dg_ctx* c, const T* resid) {
       for (int q = 4; q >= 0; --q) {
         const double ts = ti + kRkC[q] * dt;
         // lres += b ly; gradient: dt d/dm <lres, W(m) (R y_q + raw sources(ts))>
-        if (split) dga::raw_rhs_s<T><<<eg, traw, lraw, st>>>(A, ys + q * n, r);
-        else dga::raw_rhs<T><<<eg, et, lraw, st>>>(A, ys + q * n, r);
+        if constexpr (f64)
+          if (split) dga::raw_rhs_s<T><<<eg, traw, lraw, st>>>(A, ys + q * n, r);
+        if (!split) dga::raw_rhs<T><<<eg, et, lraw, st>>>(A, ys + q * n, r);
         if (ns > 0) {
           dgs::source_add<T><<<nblocks(3 * Np), 256, 0, st>>>(
               r, static_cast<T*>(nullptr), static_cast<const int64_t*>(c->src_elem.p),
@@ -1086,9 +1092,10 @@ dg_status adj_backward_t(dg_ctx* c, const T* resid) {
               ns, Np, KNp, ts, 1.0, 0.0);
         }
         // and mu = W^T lres (one kernel, which leaves a lres); then ly += dt R^T mu
-        if (split)
-          dga::grad_wadgT_s<T><<<eg, tgw, lgw, st>>>(A, lres, ly, kRkA[q], kRkB[q], r, grad, dt, mu);
-        else
+        if constexpr (f64)
+          if (split)
+            dga::grad_wadgT_s<T><<<eg, tgw, lgw, st>>>(A, lres, ly, kRkA[q], kRkB[q], r, grad, dt, mu);
+        if (!split)
           dga::grad_wadgT<T><<<eg, et, lgw, st>>>(A, lres, ly, kRkA[q], kRkB[q], r, grad, dt, mu);
         dga::liftT_faces<T><<<eg, et, l9, st>>>(A, mu, gb);
         if (upwind) {

@@ -107,7 +107,6 @@ struct TOrd {
   static_assert(Np % 4 == 0, "lanes hold four nodes");
   // the state stays in registers from phase 1 to phase 3 where they suffice
   static constexpr bool KEEPQ = N == 5;
-  static_assert(Np % 4 == 0, "lanes hold four nodes");
   // fragments of P parts (the layout of EOrd at P = 2)
   static constexpr int OFF_D = 0;
   static constexpr int OFF_L = OFF_D + 3 * RT * KN;
@@ -309,21 +308,14 @@ __device__ __forceinline__ void bt_deriv(const FragBuf& F, const bf16x8* sn, int
 }
 
 // r of the group's components into LDS.  The accumulator rows past Np are zero
-// (zero operator rows); an odd RT leaves the second half of the last K step to
-// be cleared.
+// (zero operator rows).
 template <int N, int P, int H>
 __device__ __forceinline__ void bt_rput(bf16x8* sn, int t, int g, int e, const f32x4 (&r)[9]) {
   using O = TOrd<N, P>;
   constexpr BtRole R = bt_role(O::DH, H);
 #pragma unroll
   for (int i = 0; i < R.nc; ++i) bt_put4<P>(sn, O::KN, R.c0 + i, t, g, e, r[i]);
-  if constexpr (2 * O::KN > O::RT) {
-    if (t == 0) {
-#pragma unroll
-      for (int i = 0; i < R.nc; ++i)
-        bt_put4<P>(sn, O::KN, R.c0 + i, O::RT, g, e, f32x4{0.f, 0.f, 0.f, 0.f});
-    }
-  }
+  static_assert(2 * O::KN == O::RT, "node tiles fill the K steps");
 }
 
 // The weight-adjusted mass inverse for the NC components of group grp and the K

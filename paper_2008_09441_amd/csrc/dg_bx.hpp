@@ -274,9 +274,6 @@ struct BLds {
   static constexpr int SRL = sizeof(T) == 4 ? 3 * O::SVQ * 2 * 64 * 4 : 0;
   static constexpr int SU = SF > RO + SRL ? SF : RO + SRL;
   static constexpr int OFF_U = (SQ + SG + SZ + 3) & ~3;  // 16-byte aligned union
-  // FP32: the third part of those operands, over the impedances (phase B's)
-  static constexpr int OFF_P3 = (SQ + SG + 3) & ~3;
-  static constexpr bool PARK3 = OFF_P3 + 3 * O::SVQ * 64 * 4 <= OFF_U;
   static constexpr int USED = (OFF_U + SU) * int(sizeof(T));
   // Padded so that the workgroups one CU can hold (160 KiB of LDS) never use
   // more than 128 KiB together (at most 3 per CU at >40 KiB each, 2 at
@@ -425,8 +422,7 @@ __device__ __forceinline__ void mat_chunk(const BxArgsT<T>& A, int64_t tile, int
 template <int N, int W, int P>
 __device__ __forceinline__ void quad_proj(const BxArgs& A, const FragsS<N>& F, int64_t tile, int lane,
                                           const f32x4 (&acc)[3][BOrd<N>::RT],
-                                          const f32x4 (&m0)[3][2], float* sr, bf16x8* srl,
-                                          bf16x8* srl2) {
+                                          const f32x4 (&m0)[3][2], float* sr, bf16x8* srl) {
   using O = BOrd<N>;
   constexpr int Np = O::Np, RT = O::RT, QT = O::QT, QC = O::QC, SVQ = O::SVQ;
   constexpr int NC = wave_ncomp(W);
@@ -434,13 +430,9 @@ __device__ __forceinline__ void quad_proj(const BxArgs& A, const FragsS<N>& F, i
 
   // V_q B operands: K slot 8 g + j of step s holds row 4 g + j % 4 of node
   // tile 2 s + j / 4, which is where this lane's accumulator already has it.
-  // The three-component wave parks two parts in LDS (register budget), and the
-  // third part of FP32 over the impedances where they are large enough.
-  constexpr bool park = (NC == 3);
-  constexpr int PK = !park ? 0 : P == 3 && BLds<N>::PARK3 ? 3 : 2;   // parts parked
-  auto pk = [&](int i, int s, int h) {
-    return h < 2 ? srl + ((i * SVQ + s) * 2 + h) * 64 + lane : srl2 + (i * SVQ + s) * 64 + lane;
-  };
+  // The three-component wave parks two parts in LDS (register budget).
+  constexpr int PK = NC == 3 ? 2 : 0;   // parts parked
+  auto pk = [&](int i, int s, int h) { return srl + ((i * SVQ + s) * 2 + h) * 64 + lane; };
   bf16x8 r[NC][SVQ][P];
 #pragma unroll
   for (int i = 0; i < NC; ++i)
@@ -526,7 +518,6 @@ __device__ __forceinline__ void quad_proj(const BxArgs& A, const FragsS<N>& F, i
                 w[i][u] = mma(fv[u][s][prod_a(P, k)], r[i][s][prod_b(P, k)], w[i][u]);
             }
           }
-          if (PK == 3) __builtin_amdgcn_sched_barrier(0);   // parked parts one step at a time
         }
         if constexpr (P == 3) {   // the leading products on their own
           f32x4 wl[NC];
@@ -870,7 +861,6 @@ __device__ __forceinline__ void stage_bx_run(const BxArgsT<T>& A, int64_t G, int
   T* sF = smem + L::OFF_U;        // [9][NF4][17]  (phases B, C)
   T* sr = sF;                     // [9][Np][17]   (phases D, E)
   bf16x8* srl = reinterpret_cast<bf16x8*>(sF + L::RO);   // wave 2, phase D
-  bf16x8* srl2 = reinterpret_cast<bf16x8*>(smem + L::OFF_P3);
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -1113,10 +1103,10 @@ __device__ __forceinline__ void stage_bx_run(const BxArgsT<T>& A, int64_t G, int
     }
   } else {
     switch (grp) {
-      case 0: quad_proj<N, 0, NP>(A, F, tile, lane, acc, m0, sr, srl, srl2); break;
-      case 1: quad_proj<N, 1, NP>(A, F, tile, lane, acc, m0, sr, srl, srl2); break;
-      case 2: quad_proj<N, 2, NP>(A, F, tile, lane, acc, m0, sr, srl, srl2); break;
-      default: quad_proj<N, 3, NP>(A, F, tile, lane, acc, m0, sr, srl, srl2); break;
+      case 0: quad_proj<N, 0, NP>(A, F, tile, lane, acc, m0, sr, srl); break;
+      case 1: quad_proj<N, 1, NP>(A, F, tile, lane, acc, m0, sr, srl); break;
+      case 2: quad_proj<N, 2, NP>(A, F, tile, lane, acc, m0, sr, srl); break;
+      default: quad_proj<N, 3, NP>(A, F, tile, lane, acc, m0, sr, srl); break;
     }
   }
 
@@ -1176,8 +1166,8 @@ __global__ __launch_bounds__(kThreads, bx_waves(N)) void stage_bx(BxArgs A) {
   stage_bx_run<N, F32>(A, gridDim.x, blockIdx.x);
 }
 
-// The FP32 stage on FP32 products at every order (FOrd fragments): the forward
-// run and the replay of the discrete adjoint.  The face-node jumps that its
+// The FP32 stage on FP32 products at orders 3 and 4 (FOrd fragments), as stage_bx
+// takes them at orders 1 and 2: the forward run of the discrete adjoint.  The face-node jumps that its
 // gradients are made of cancel to 1e-5 of the state, so that another rounding of
 // the states changes an FP32 gradient by 1e-5 to 1e-3 of its norm, as much as its
 // own error; the adjoint therefore keeps these products in all of its parts.

@@ -28,7 +28,7 @@ std::vector<float> mfma_fragments_f32(const RefElement& re);
 // fragments of the one-element-per-workgroup stage, orders 2-7: BF16x3 in the
 // layout of EOrd, FP32 and FP64 in that of EFOrd (at orders 5-7 BF16x3 and FP64
 // are those of mfma_fragments and _f64).  Contexts take it at orders 5-7, in FP64
-// also at orders 2-4.
+// also at orders 2-4 (there in BF16x3 and FP32 only the CPU emulation runs it).
 std::vector<uint16_t> element_fragments(const RefElement& re);
 std::vector<float> element_fragments_f32(const RefElement& re);
 std::vector<double> element_fragments_f64(const RefElement& re);

@@ -94,7 +94,9 @@ DG_INST stage_bx<DG_ORDER, DG_PART == 1>(const dgb::BxArgs&, unsigned, hipStream
 #elif DG_PART == 2
 DG_INST stage_bx_d<DG_ORDER>(const dgb::BxArgsT<double>&, unsigned, hipStream_t);
 #else
+#if DG_ORDER >= 3
 DG_INST stage_bx_p<DG_ORDER>(const dgb::BxArgs&, unsigned, hipStream_t);
+#endif
 DG_INST stage_bx_r<DG_ORDER>(const dgb::BxArgs&, unsigned, hipStream_t);
 DG_INST adj_tile<DG_ORDER>(const dgt::TileArgs&, unsigned, hipStream_t);
 #endif
