@@ -112,8 +112,8 @@ def parse():
 
 
 def stage_kernel_name(precision, N):
-    """The kernel one stage launches for this precision and order (orders 5-7:
-    below 72 tiles of 16 elements; see large_mesh_kernel_name)."""
+    """The kernel one stage launches for this precision and order (orders 5-7: on
+    small meshes; see large_mesh_kernel_name)."""
     if precision == "bf16x3":
         return f"stage_bx<{N}>" if N <= 4 else f"stage_be<{N}>"
     if precision == "fp32":
@@ -122,7 +122,7 @@ def stage_kernel_name(precision, N):
 
 
 def large_mesh_kernel_name(precision, N):
-    """The kernel one stage launches from 72 tiles of 16 elements on."""
+    """The kernel one stage launches from 160 tiles of 16 elements on."""
     if precision == "bf16x3" and N >= 5:
         return f"stage_bt<{N},2>"
     if precision == "fp32" and N in (5, 6):
@@ -711,14 +711,17 @@ def main():
         sec32, q32 = other_path("fp32")
         out["fp32_path"] = {"value": dofs * args.steps / sec32,
                             "ms_per_step": sec32 / args.steps * 1e3,
-                            "kernel": stage_kernel_name("fp32", N)}
-        # FP32 matrix cores: dense contraction flops of an element-stage
-        # (D_r, D_s, D_t, LIFT, V_q, P_q over nine fields) per launch
+                            "kernel": large_mesh_kernel_name("fp32", N)}
+        # dense contraction flops of an element-stage (D_r, D_s, D_t, LIFT, V_q,
+        # P_q over nine fields) per launch, against the rate of the products that
+        # the kernel runs: six bf16 products each at orders 3-6 (2,500 TFLOP/s
+        # dense), else FP32 products
         Np, Nfp, Nq = (N + 1) * (N + 2) * (N + 3) // 6, (N + 1) * (N + 2) // 2, (N + 1) ** 3
         flop = 2 * 9 * (3 * Np * Np + Np * 4 * Nfp + 2 * Nq * Np)
         a32 = flop * K / (sec32 / (5 * args.steps)) / 1e12
-        out["fp32_path"]["roofline"] = {"bound": "mfma", "achieved": a32, "peak": 157.3,
-                                        "unit": "TFLOP/s", "frac": a32 / 157.3,
+        p32 = 2500.0 / 6 if 3 <= N <= 6 else 157.3
+        out["fp32_path"]["roofline"] = {"bound": "mfma", "achieved": a32, "peak": p32,
+                                        "unit": "TFLOP/s", "frac": a32 / p32,
                                         "flop_per_element_stage": flop}
         progress("fp32 path timed")
     if not args.no_fp64_reference and args.precision != "fp64":

@@ -56,8 +56,14 @@ typedef enum {
 
 /* DG_FP64: FP64 state and arithmetic (the dense contractions on the FP64
  * matrix cores, 16x16x4 products, at every order).
- * DG_FP32: FP32 state and arithmetic, with the
- * dense contractions on the FP32 matrix cores (16x16x4 products).
+ * DG_FP32: FP32 state and arithmetic.  The dense contractions run on the FP32
+ * matrix cores (16x16x4 products) at orders 1, 2 and 7, on small meshes of
+ * orders 5 and 6 and in the discrete adjoint, else as split products of three
+ * bf16 parts per operand (24 bits, the whole of an FP32 value) with FP32
+ * accumulation, as close to FP64 as FP32 products: values are whole in three
+ * parts from about 1e-33 up, and one that FP32 holds but bf16 rounds to
+ * infinity (above 3.39e38) or that is not finite makes its element's results
+ * NaN.
  * DG_FP32_BF16X3: FP32 state, the dense contractions as split products of
  * bf16 hi/lo parts on the matrix cores with FP32 accumulation (three
  * products each, about 2^-16 relative error per product). */
@@ -279,7 +285,10 @@ dg_status dg_material_set_weights(dg_ctx* ctx, const double* irho_q, const doubl
  * keeping a copy of the state every `every` steps on the device and writing
  * the receiver velocities after every step to trace (host
  * [nsteps][nrec][3], working precision).  Leaves the context at the end of
- * the run.  Needs receivers (DG_ESTATE).  Library-owned device memory:
+ * the run.  FP32 contexts take FP32 products here at every order and size, as
+ * the reverse sweep does (the face-node jumps behind its gradients cancel to
+ * 1e-5 of the state), so that from order 3 on the trace and the final state may
+ * differ in rounding from those of dg_run and dg_run_record.  Needs receivers (DG_ESTATE).  Library-owned device memory:
  * ceil(nsteps/every) + 5 every + 5 states (FP32 at orders 1-4: 10 every + 5,
  * the replay also keeping R y of every stage input, or 20 every + 5 when
  * that much fits, so that the replay of the next interval overlaps the

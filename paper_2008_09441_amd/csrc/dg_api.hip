@@ -178,6 +178,9 @@ bool tiled_mfma(const dg_ctx* c) {
 //   FP64 is never batched, so its lines are where one context is faster, us per
 // stage (tiles, elements): order 2 8.8, 7.0 at 162 elements; order 3 18.5, 11.3
 // at 384 and 18.6, 15.0 at 750; order 4 39.2, 15.6 at 384 and 39.6, 21.2 at 750.
+// Four contexts at once on streams of their own gain as long as they are small
+// (384 elements: order 3 37.4, 27.2 for all four; order 4 41.7, 33.5) and lose near
+// the line (750: 21.9, 41.5; 42.8, 61.2); two lose nowhere more than 10%.
 //   FP32 and BF16x3 contexts may be batched, and a batch fills the chip with
 // the tiles of all of its contexts.  At orders 2-4 an element then costs three to
 // five times as much in a workgroup of its own as in a tile (eight contexts of
