@@ -7,7 +7,9 @@
 // written x = hi + lo with hi = bf16(x), lo = bf16(x - hi), and
 // A B ~ A_hi B_hi + A_hi B_lo + A_lo B_hi with FP32 accumulation (relative
 // error ~2^-16 per product).  Fluxes, the chain rule, material weights and
-// the LSRK(5,4) update [CK94] are FP32.
+// the LSRK(5,4) update [CK94] are FP32.  FP32 runs the same phases on three bf16
+// parts at orders 3 and 4 (see kProd) and on FP32 products at orders 1 and 2 and
+// in the adjoint, FP64 in double precision on the FP64 products.
 //
 // One workgroup (four waves) owns a tile of 16 consecutive elements; the
 // MFMA column index is the element, so a lane keeps the same element through
