@@ -20,7 +20,7 @@
 //
 // Measured against one element per workgroup (dg_be.hpp), us per stage on
 // 24,576 elements: BF16x3 order 5 307 -> 109, order 6 593 -> 292, order 7
-// 926 -> 402; FP32 order 5 464 -> 163, order 6 1006 -> 371.  The relative error
+// 926 -> 402; FP32 order 5 464 -> 173, order 6 1006 -> 376.  The relative error
 // of an FP32 right-hand side of a smooth state against FP64 went from 1.23e-6 to
 // 6.9e-7 (order 5) and from 1.77e-6 to 9.5e-7 (order 6).
 // What bounds it now (order 7, cycles of a workgroup's 151,000): state and
