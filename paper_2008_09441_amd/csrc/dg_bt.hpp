@@ -336,8 +336,11 @@ __device__ __forceinline__ void bt_quad(const BeArgs& A, const FragBuf& F, const
   // the two weights: lam and mu for the normal stresses (lam tr + 2 mu), else
   // 1/rho or 2 mu for each of two components (three components share the first)
   const int c0 = bt_comp(O::G, grp, 0), c1 = bt_comp(O::G, grp, 1);
-  const float* wf[2] = {(normal ? A.lam : c0 < 3 ? A.irho : A.mu) + e0 * Nq,
-                        (normal ? A.mu : c1 < 3 ? A.irho : A.mu) + e0 * Nq};
+  // (values first: a choice between the fields of A would keep a batch's copy of
+  // it in memory)
+  const float *irho = A.irho, *lam = A.lam, *mu = A.mu;
+  const float* wf[2] = {(normal ? lam : c0 < 3 ? irho : mu) + e0 * Nq,
+                        (normal ? mu : c1 < 3 ? irho : mu) + e0 * Nq};
   const float ws[2] = {!normal && c0 >= 3 ? 2.f : 1.f, normal || c1 >= 3 ? 2.f : 1.f};
   auto weights = [&](int c, f32x4 (&m)[2][2]) {
 #pragma unroll
