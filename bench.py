@@ -122,7 +122,7 @@ def stage_kernel_name(precision, N):
 
 
 def large_mesh_kernel_name(precision, N):
-    """The kernel one stage launches from 160 tiles of 16 elements on."""
+    """The kernel one stage launches from 128 tiles of 16 elements on."""
     if precision == "bf16x3" and N >= 5:
         return f"stage_bt<{N},2>"
     if precision == "fp32" and N in (5, 6):

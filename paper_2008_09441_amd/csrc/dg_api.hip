@@ -190,10 +190,10 @@ bool tiled_mfma(const dg_ctx* c) {
 //   At orders 5-7 a batch of both kinds takes two launches a stage, one after the
 // other.  The lines are where a tile context saves more than that costs beside
 // any others, us per stage with a context of 162 elements (all elements, tiles
-// and elements): BF16x3 order 5 35.6, 36.5 at 1,800 elements and 38.5, 37.5 at
-// 2,058, order 6 73.7, 76.1 at 2,304 and 80.1, 77.5 at 2,592, order 7 69.5, 76.3
-// at 1,296 and 83.2, 76.6 at 1,536; FP32 order 5 37.9, 39.0 at 1,296 and 44.4,
-// 39.2 at 1,536, order 6 92.2, 96.5 at 1,536 and 103.5, 97.1 at 1,800.
+// and elements): BF16x3 order 5 35.8, 36.4 at 1,800 elements and 39.1, 37.6 at
+// 2,058, order 6 60.7, 62.2 at 1,800 and 66.2, 62.2 at 2,028, order 7 70.1, 76.1
+// at 1,296 and 82.1, 76.5 at 1,536; FP32 order 5 38.6, 39.0 at 1,296 and 44.9,
+// 39.0 at 1,536, order 6 78.5, 82.7 at 1,296 and 92.8, 83.6 at 1,536.
 //   At order 1 tiles are never slower.  FP64 at orders 5-7 and FP32 at order 7
 // have no tile kernel (their tiles need more than the 128 KiB of LDS that a
 // workgroup takes here).
@@ -201,8 +201,8 @@ bool one_element(int32_t precision, int order, int64_t K) {
   constexpr int64_t always = INT64_MAX;
   // tiles from which on a context runs tiles, by order 1-7
   static constexpr int64_t fp64[] = {0, 24, 48, 64, always, always, always};
-  static constexpr int64_t fp32[] = {0, 0, 0, 0, 96, 112, always};
-  static constexpr int64_t bf16x3[] = {0, 0, 0, 0, 128, 160, 96};
+  static constexpr int64_t fp32[] = {0, 0, 0, 0, 96, 96, always};
+  static constexpr int64_t bf16x3[] = {0, 0, 0, 0, 128, 128, 96};
   const int64_t* least = precision == DG_FP64 ? fp64 : precision == DG_FP32 ? fp32 : bf16x3;
   return (K + dgb::kTile - 1) / dgb::kTile < least[order - 1];
 }

@@ -25,8 +25,8 @@ def _need_gpu():
 
 
 # with a ragged last tile (K = 6 n^3 + 3).  FP64 takes tiles from 24, 48 and 64
-# tiles on at orders 2-4, the others at every size; orders 5-7 from 96 (order 5
-# FP32, order 7), 112 (order 6 FP32), 128 and 160 (orders 5 and 6 BF16x3) on
+# tiles on at orders 2-4, the others at every size; orders 5-7 from 96 (FP32,
+# order 7) and 128 (orders 5 and 6 BF16x3) on
 @pytest.mark.parametrize("n,N,precision,flux", [
     (3, 1, "fp64", "central"), (5, 2, "fp64", "central"), (6, 3, "fp64", "central"),
     (6, 4, "fp64", "central"), (3, 1, "fp32", "central"), (3, 2, "fp32", "central"),
